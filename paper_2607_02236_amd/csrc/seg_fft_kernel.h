@@ -95,12 +95,22 @@ struct FftShape<200> {
 #define TACAW_WAVES_PER_EU 1  // minimum waves per SIMD the register allocation must allow
 #endif
 // FULL (whole-series variants only): hop = L, no overlap; otherwise hop = L/2 there.
-template <int L, typename InT, bool SUB64, bool DP, int MODE, bool FULL = false>
+// MIX (MODE 1 and 3): the launch's first chunk starts before the push (a series
+// pushed in pieces), so frames before push_begin come from the per-frame ring.
+// Only that chunk can: the chunk before it was complete when the push came, so
+// with hop L/2 or L every later chunk's new frames lie in the push, and the
+// whole-series loop serves it with one more load path for each probe's first
+// chunk. Lanes of a row group choose the ring or the push by their frame, so a
+// push may begin anywhere. Before, every launch of a pushed series took the general
+// variant (no prefetch, per-lane 64-bit addresses, 160 bytes of scratch per thread):
+// 4 probes of 383^2 pixels in pushes of 200 frames, L = 200: 1321 us a launch with the general variant, 988 us with this one.
+template <int L, typename InT, bool SUB64, bool DP, int MODE, bool FULL = false, bool MIX = false>
 __global__ void __launch_bounds__(FftShape<L>::W*(L / FftShape<L>::N1))
     __attribute__((amdgpu_waves_per_eu(TACAW_WAVES_PER_EU)))
     seg_fft_kernel(const SegArgs a) {
   constexpr bool LEAN = MODE != 0;
   static_assert(LEAN || !FULL, "hop = L is a whole-series variant");
+  static_assert(!MIX || MODE == 1 || MODE == 3, "ring and push: the push-buffer variants");
   constexpr bool TILED = MODE == 4;
   constexpr bool RING = MODE == 2 || TILED;
   constexpr bool NARROW = MODE == 3;
@@ -222,9 +232,26 @@ __global__ void __launch_bounds__(FftShape<L>::W*(L / FftShape<L>::N1))
     }
     return buffer_load<InT>(rb, group_bytes, lane_off);
   };
+  // sample n1 of the launch's first chunk of probe probe0 + ii; ring rows are
+  // contiguous frames, and a row group (N2 frames, N2 dividing H and the depth)
+  // does not wrap
+  const uint32_t ring_off = MIX ? (uint32_t)(((int64_t)n2 * n_k + kc) * ESZ) : 0u;
+  const uint32_t ring_bytes = MIX ? (uint32_t)((int64_t)N2 * n_k * ESZ) : 0u;
+  auto fetch_first = [&](int ii, int n1) -> InT {
+    if constexpr (MIX) {
+      const int64_t f0 = (int64_t)a.s_lo * H + N2 * n1;
+      if (f0 + n2 < a.push_begin) {
+        const int64_t slot = (a.probe0 + ii) % a.n_slots;
+        const char* rb =
+            (const char*)a.ring + (slot * a.ring_depth + f0 % a.ring_depth) * n_k * ESZ;
+        return buffer_load<InT>(rb, ring_bytes, ring_off);
+      }
+    }
+    return fetch_at(ii, a.s_lo, n1);
+  };
   if constexpr (LEAN) {
 #pragma unroll
-    for (int n1 = 0; n1 < N1; ++n1) pre[n1] = fetch_at(0, a.s_lo, n1);
+    for (int n1 = 0; n1 < N1; ++n1) pre[n1] = fetch_first(0, n1);
   }
 
   int cc = 0;  // chunks processed by this thread block (selects the exchange tile)
@@ -386,7 +413,8 @@ __global__ void __launch_bounds__(FftShape<L>::W*(L / FftShape<L>::N1))
           const int ss = next_chunk ? s + 1 : a.s_lo;
 #pragma unroll
           for (int n1 = 0; n1 < N1; ++n1)
-            if (n1 >= HALF || !next_chunk || FULL) pre[n1] = fetch_at(ii, ss, n1);
+            if (n1 >= HALF || !next_chunk || FULL)
+              pre[n1] = MIX && !next_chunk ? fetch_first(ii, n1) : fetch_at(ii, ss, n1);
         }
       } else if (have_kept && half_hop) {
         // the kept half was counted in the previous chunk; the new half all counts
@@ -500,7 +528,9 @@ __global__ void __launch_bounds__(FftShape<L>::W*(L / FftShape<L>::N1))
           auto cl = [&](int n) { return col[n * W]; };
           if (gg == 0) dif_combine<N1, 2, 0>(cl, X);
           else dif_combine<N1, 2, 1>(cl, X);
-        } else if constexpr (!LEAN) {
+        } else if constexpr (!LEAN || MIX) {
+          // (a pushed series: one code path for every chunk of it, as the roundings of
+          // the two G = 4 paths differ in the twiddle row)
           auto cl = [&](int n) { return col[n * W]; };
           if (gg == 0) dif_combine<N1, 4, 0>(cl, X);
           else if (gg == 1) dif_combine<N1, 4, 1>(cl, X);

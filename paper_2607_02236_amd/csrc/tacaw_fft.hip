@@ -5,40 +5,58 @@
 
 namespace tacaw {
 
-template <int L, typename InT, bool SUB64, bool FULL>
-static void launch_lean(const SegArgs& a, bool narrow, int n_tiles, hipStream_t st) {
+template <int L, typename InT, bool SUB64, int MODE, bool FULL, bool MIX>
+static void launch_lean(const SegArgs& a, int n_tiles, hipStream_t st) {
   constexpr int NT = FftShape<L>::W * (L / FftShape<L>::N1);
-  if (narrow) {
-    if (a.n_det > 0)
-      hipLaunchKernelGGL((seg_fft_kernel<L, InT, SUB64, true, 3, FULL>), dim3(n_tiles), dim3(NT), 0, st, a);
-    else
-      hipLaunchKernelGGL((seg_fft_kernel<L, InT, SUB64, false, 3, FULL>), dim3(n_tiles), dim3(NT), 0, st, a);
-  } else {
-    if (a.n_det > 0)
-      hipLaunchKernelGGL((seg_fft_kernel<L, InT, SUB64, true, 1, FULL>), dim3(n_tiles), dim3(NT), 0, st, a);
-    else
-      hipLaunchKernelGGL((seg_fft_kernel<L, InT, SUB64, false, 1, FULL>), dim3(n_tiles), dim3(NT), 0, st, a);
-  }
+  if (a.n_det > 0)
+    hipLaunchKernelGGL((seg_fft_kernel<L, InT, SUB64, true, MODE, FULL, MIX>), dim3(n_tiles),
+                       dim3(NT), 0, st, a);
+  else
+    hipLaunchKernelGGL((seg_fft_kernel<L, InT, SUB64, false, MODE, FULL, MIX>), dim3(n_tiles),
+                       dim3(NT), 0, st, a);
 }
 
 template <int L, typename InT, bool SUB64>
 static hipError_t launch_t(const SegArgs& a, int n_tiles, hipStream_t st) {
   constexpr int NT = FftShape<L>::W * (L / FftShape<L>::N1);
-  const bool lean = (2 * a.hop == L || a.hop == L) && !a.from_ring &&
-                    (int64_t)a.s_lo * a.hop >= a.push_begin;
+  constexpr int N2 = L / FftShape<L>::N1;
+  const bool lean = (2 * a.hop == L || a.hop == L) && !a.from_ring;
+  // frames before the push, in the first chunk only (see MIX)
+  const bool mix = lean && (int64_t)a.s_lo * a.hop < a.push_begin;
   // one descriptor per chunk when a chunk's frames span less than 2 GiB
   const int64_t span = pix_off((int64_t)a.n_k - 1, a.nx, a.row_stride) + 1;
   const bool narrow =
       ((int64_t)(L - 1) * a.fstride + span) * (int64_t)sizeof(InT) < ((int64_t)1 << 31);
-  if (lean) {
-    if (a.hop == L) launch_lean<L, InT, SUB64, true>(a, narrow, n_tiles, st);
-    else launch_lean<L, InT, SUB64, false>(a, narrow, n_tiles, st);
-  } else {
-    if (a.n_det > 0)
-      hipLaunchKernelGGL((seg_fft_kernel<L, InT, SUB64, true, 0>), dim3(n_tiles), dim3(NT), 0, st, a);
-    else
-      hipLaunchKernelGGL((seg_fft_kernel<L, InT, SUB64, false, 0>), dim3(n_tiles), dim3(NT), 0, st, a);
+  // the ring's row groups are addressed with 31-bit offsets; the float2 form with
+  // FP64 differences (exact mean) takes each series in one push
+  constexpr bool kMixed = !(SUB64 && sizeof(InT) == 8);
+  const bool ring_fits = (int64_t)N2 * a.n_k * (int64_t)sizeof(InT) < ((int64_t)1 << 31);
+  if (lean && !mix) {
+    if (a.hop == L) {
+      if (narrow) launch_lean<L, InT, SUB64, 3, true, false>(a, n_tiles, st);
+      else launch_lean<L, InT, SUB64, 1, true, false>(a, n_tiles, st);
+    } else {
+      if (narrow) launch_lean<L, InT, SUB64, 3, false, false>(a, n_tiles, st);
+      else launch_lean<L, InT, SUB64, 1, false, false>(a, n_tiles, st);
+    }
+    return hipGetLastError();
   }
+  if constexpr (kMixed) {
+    if (mix && ring_fits) {
+      if (a.hop == L) {
+        if (narrow) launch_lean<L, InT, SUB64, 3, true, true>(a, n_tiles, st);
+        else launch_lean<L, InT, SUB64, 1, true, true>(a, n_tiles, st);
+      } else {
+        if (narrow) launch_lean<L, InT, SUB64, 3, false, true>(a, n_tiles, st);
+        else launch_lean<L, InT, SUB64, 1, false, true>(a, n_tiles, st);
+      }
+      return hipGetLastError();
+    }
+  }
+  if (a.n_det > 0)
+    hipLaunchKernelGGL((seg_fft_kernel<L, InT, SUB64, true, 0>), dim3(n_tiles), dim3(NT), 0, st, a);
+  else
+    hipLaunchKernelGGL((seg_fft_kernel<L, InT, SUB64, false, 0>), dim3(n_tiles), dim3(NT), 0, st, a);
   return hipGetLastError();
 }
 
