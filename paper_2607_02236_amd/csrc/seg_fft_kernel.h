@@ -88,9 +88,6 @@ struct FftShape<200> {
 // variant reading every frame from the ring (deferred streaming); MODE 3: MODE 1
 // when a whole chunk of frames spans less than 2 GiB, so one buffer descriptor per
 // chunk serves all row groups through a scalar offset (fewer scalar registers).
-#ifndef TACAW_XBUF_TILES
-#define TACAW_XBUF_TILES 2  // exchange tiles: 2 = alternate per chunk (one barrier), 1 = two barriers
-#endif
 #ifndef TACAW_WAVES_PER_EU
 #define TACAW_WAVES_PER_EU 1  // minimum waves per SIMD the register allocation must allow
 #endif
@@ -129,10 +126,16 @@ __global__ void __launch_bounds__(FftShape<L>::W*(L / FftShape<L>::N1))
   static_assert(G == 1 || G == 2 || G == 4, "pass-2 split factor");
 
   // two exchange tiles [k1][n2][px] used by alternate chunks, so one barrier per
-  // chunk suffices; tile 0 is reused for the per-probe reductions
-  constexpr int NBUF = TACAW_XBUF_TILES;
-  __shared__ float2 xbuf2[NBUF * N1 * KROW];
-  float2* const xbuf = xbuf2;
+  // chunk suffices; the per-probe reductions take the tile whose turn it is
+  // detector staging of a probe in one tile: row m of W doubles at m W + m / RB, so
+  // that 32 consecutive rows read at one pixel fall on distinct banks
+  constexpr int RB = 32 / W;
+  constexpr int SP = L * W + L / RB;
+  constexpr int TILE = N1 * KROW > SP ? N1 * KROW : SP;
+  __shared__ float2 xbuf2[2 * TILE];
+  // partial mean sums, one per wave and pixel, of alternate probes
+  constexpr int NRED = NT / 64 * W;
+  __shared__ double2 s_red[2 * NRED];
   __shared__ float2 s_tw[L];          // [n2][k1]
   __shared__ float s_win[L];          // [n2][n1]
   __shared__ double s_mask[DP ? kMaxDet * W : 1];
@@ -254,12 +257,39 @@ __global__ void __launch_bounds__(FftShape<L>::W*(L / FftShape<L>::N1))
     for (int n1 = 0; n1 < N1; ++n1) pre[n1] = fetch_first(0, n1);
   }
 
+  // FP64 sums in global memory: stored by the launch that holds the probe's first
+  // chunk, added (without reading them back) by later ones
+  auto put = [&](double2* dst, double2 val) {
+    if (a.s_lo == 0) {
+      *dst = val;
+    } else {
+      unsafeAtomicAdd(&dst->x, val.x);
+      unsafeAtomicAdd(&dst->y, val.y);
+    }
+  };
+  // mean sum of probe probe0 + ii from its waves' partial sums
+  auto put_msum = [&](int ii) {
+    if (n2 == 0 && kvalid) {
+      const double2* red = s_red + (ii & 1) * NRED + px;
+      double2 t = red[0];
+#pragma unroll
+      for (int r = 1; r < NT / 64; ++r) {
+        t.x += red[r * W].x;
+        t.y += red[r * W].y;
+      }
+      put(a.msum + (int64_t)(a.probe0 + ii) * n_k + k, t);
+    }
+  };
   int cc = 0;  // chunks processed by this thread block (selects the exchange tile)
+  // reference c: fixed by the probe's first chunk (make_ref below) or read back, one
+  // probe ahead
+  const bool read_ref = !(track && a.s_lo == 0);
+  double2 cr_next = make_double2(0.0, 0.0);
+  if (read_ref) cr_next = a.cref[(int64_t)a.probe0 * n_k + kc];
   for (int i = 0; i < a.n_probes; ++i) {
     const int p = a.probe0 + i;
-    // reference c: fixed by the probe's first chunk (make_ref below) or read back
-    double2 cr = make_double2(0.0, 0.0);
-    if (!(track && a.s_lo == 0)) cr = a.cref[(int64_t)p * n_k + kc];
+    double2 cr = cr_next;
+    if (read_ref && i + 1 < a.n_probes) cr_next = a.cref[(int64_t)(p + 1) * n_k + kc];
     float2 cf = make_float2((float)cr.x, (float)cr.y);
     const char* in_probe = (const char*)a.in + (int64_t)i * a.pstride * ESZ;
     const InT* ringb =
@@ -466,9 +496,8 @@ __global__ void __launch_bounds__(FftShape<L>::W*(L / FftShape<L>::N1))
       // tile (cc & 1), cc counting this thread block's chunks: the reads of
       // chunk cc - 2 from it finished before the barrier of chunk cc - 1, so only
       // the barrier after the writes is needed
-      float2* const xb = xbuf2 + (NBUF == 2 ? (cc & 1) : 0) * (N1 * KROW);
+      float2* const xb = xbuf2 + (cc & 1) * TILE;
       ++cc;
-      if constexpr (NBUF == 1) __syncthreads();  // the previous chunk's reads are done
 #pragma unroll
       for (int k1 = 0; k1 < N1; ++k1) xb[k1 * KROW + n2 * W + px] = v[k1];
       __syncthreads();
@@ -586,66 +615,60 @@ __global__ void __launch_bounds__(FftShape<L>::W*(L / FftShape<L>::N1))
       }
     }
 
+    // Per-probe sums: nothing here waits for memory, and only the detector partials
+    // have a barrier of their own (five before, sums read back from memory, and LDS
+    // reads of staged rows that fell on one bank pair): 4 probes of 383^2 pixels in
+    // pushes of 200 frames, L = 200, where a launch holds two chunks per probe, 988 ->
+    // 827 us a launch; 32 probes of 256^2, L = 512, 7 chunks per probe, -0.6 to -1.9 % of the
+    // whole pass. Tiles that no mask covers stage their sums too: skipping them left
+    // neighbouring tiles out of step and cost 1 % (their frames share DRAM pages).
     if (track) {
-      __syncthreads();
-      double2* red = reinterpret_cast<double2*>(xbuf);
-      red[tid] = msum;
-      __syncthreads();
-      if (n2 == 0 && kvalid) {
-        double2 t = make_double2(0.0, 0.0);
+      // mean sum over the wave's roles (lanes W apart), then one value per wave and
+      // pixel; put_msum adds those a probe later, behind the next chunk's barrier
+      if (i > 0) put_msum(i - 1);
 #pragma unroll
-        for (int r = 0; r < N2; ++r) {
-          t.x += red[r * W + px].x;
-          t.y += red[r * W + px].y;
-        }
-        double2* ms = a.msum + (int64_t)p * n_k + k;
-        double2 o = *ms;
-        o.x += t.x;
-        o.y += t.y;
-        *ms = o;
+      for (int o = W; o < 64; o *= 2) {
+        msum.x += __shfl_xor(msum.x, o, 64);
+        msum.y += __shfl_xor(msum.y, o, 64);
       }
-      if (corr_own && kvalid) {
-        double2* xp = a.xs + ((int64_t)p * kMaxCorr + corr_b) * n_k + k;
-        double2 o = *xp;
-        o.x += xsum.x;
-        o.y += xsum.y;
-        *xp = o;
-      }
+      if ((tid & 63) < W) s_red[(i & 1) * NRED + (tid >> 6) * W + px] = msum;
+      if (corr_own && kvalid) put(a.xs + ((int64_t)p * kMaxCorr + corr_b) * n_k + k, xsum);
     }
-
     if constexpr (DP) {
-      // detector partials: the mask-weighted tile sum of the FP64 accumulator,
-      // cumulative over this launch's probes (the reduce kernel differences them)
-      __syncthreads();
-      double* sp = reinterpret_cast<double*>(xbuf);  // [L][W]
+      // staged in the tile that the last chunk did not use: its reads ended before
+      // that chunk's barrier, and the next chunk takes the other one
+      double* const sp = reinterpret_cast<double*>(xbuf2 + (cc & 1) * TILE);
+      ++cc;
+      const int jm = (G == 1) ? j : k1g + N1 * gg;
 #pragma unroll
       for (int t = 0; t < N1; ++t) {
-        const int m = (G == 1) ? (j + N2 * (t / N2)) + N1 * (t % N2) : k1g + N1 * (G * t + gg);
-        sp[m * W + px] = acc[t];
+        // bin m = jm + c, c a multiple of RB known at compile time
+        const int c = (G == 1) ? N2 * (t / N2) + N1 * (t % N2) : N1 * G * t;
+        sp[jm * W + jm / RB + px + c * W + c / RB] = acc[t];
       }
       __syncthreads();
+      // detector partials: the mask-weighted tile sum of the FP64 accumulator,
+      // cumulative over this launch's probes (the reduce kernel differences them)
       const int n_om = a.n_om;
       const int32_t* slots = a.pair_slot + (int64_t)tile * a.n_det;
-      for (int r = tid; r < n_om; r += NT) {
-        int m = r - a.roi_half;  // output row r holds bin m
-        if (m < 0) m += L;
-        double pv[W];
-#pragma unroll
-        for (int x = 0; x < W; ++x) pv[x] = sp[m * W + x];
 #pragma unroll 1
-        for (int d = 0; d < a.n_det; ++d) {
-          const int slot = slots[d];  // uniform; -1: this detector's mask is zero here
-          if (slot < 0) continue;
+      for (int d = 0; d < a.n_det; ++d) {
+        const int slot = slots[d];  // uniform; -1: this detector's mask is zero here
+        if (slot < 0) continue;
+        for (int r = tid; r < n_om; r += NT) {
+          int m = r - a.roi_half;  // output row r holds bin m
+          if (m < 0) m += L;
           double dsum = 0.0;
-#pragma unroll
-          for (int x = 0; x < W; ++x) dsum += s_mask[d * W + x] * pv[x];
-          // cumulative over the launch's probes 0..i
+#pragma unroll 8
+          for (int x = 0; x < W; ++x) dsum += s_mask[d * W + x] * sp[m * W + m / RB + x];
           a.dpart[((int64_t)slot * a.n_probes + i) * n_om + r] = dsum;
         }
       }
     }
-    // the reductions above used tile 0, which a later chunk writes
+  }
+  if (track) {
     __syncthreads();
+    put_msum(a.n_probes - 1);
   }
 
   if (kvalid) {
