@@ -73,34 +73,63 @@ hipError_t launch_ref_sampled(const void* in, int in_dtype, int64_t pstride, int
   return hipGetLastError();
 }
 
-// Exact FP64 time mean over frames [0, n_used) of each (probe, pixel).
+// Exact FP64 time mean over frames [0, n_used) of each (probe, pixel). Bound by the
+// read of the series. A block takes 64 adjacent pixels (512-byte runs of each frame)
+// and splits the frames over its kMeanGroups waves, kMeanLoads loads in flight per
+// thread; the waves' FP64 sums are added in order through LDS. With one thread per
+// pixel for all frames a small grid left the chip idle: 3200 frames of 383^2 pixels
+// 1580 -> 704 us (5.3 TB/s), 4 probes x 1024 frames of 48 x 40 268 -> 12 us.
+constexpr int kMeanGroups = 16, kMeanLoads = 8;
 template <typename InT>
-__global__ void mean_kernel(const InT* in, int64_t pstride, int64_t fstride, int32_t nx, int64_t rs,
-                            int64_t n_used, int32_t probe0, int32_t n_probes, int32_t n_k,
-                            double2* out) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(64 * kMeanGroups) mean_kernel(
+    const InT* __restrict__ in, int64_t pstride, int64_t fstride, int32_t nx, int64_t rs,
+    int64_t n_used, int32_t probe0, int32_t n_probes, int32_t n_k, double2* __restrict__ out) {
+  __shared__ double2 part[kMeanGroups][64];
+  const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+  const int64_t k = (int64_t)blockIdx.x * 64 + lane;
   const int i = blockIdx.y;
-  if (k >= n_k || i >= n_probes) return;
-  const InT* p = in + (int64_t)i * pstride + pix_off(k, nx, rs);
+  const bool valid = k < n_k;
+  const InT* p = in + (int64_t)i * pstride + pix_off(valid ? k : n_k - 1, nx, rs);
   double sx = 0.0, sy = 0.0;
-  for (int64_t n = 0; n < n_used; ++n) {
+  int64_t n = g;
+  for (; n + (kMeanLoads - 1) * kMeanGroups < n_used; n += kMeanLoads * kMeanGroups) {
+    InT v[kMeanLoads];
+#pragma unroll
+    for (int u = 0; u < kMeanLoads; ++u) v[u] = p[(n + u * kMeanGroups) * fstride];
+#pragma unroll
+    for (int u = 0; u < kMeanLoads; ++u) {
+      sx += (double)v[u].x;
+      sy += (double)v[u].y;
+    }
+  }
+  for (; n < n_used; n += kMeanGroups) {
     const InT v = p[n * fstride];
     sx += (double)v.x;
     sy += (double)v.y;
   }
-  out[(int64_t)(probe0 + i) * n_k + k] = make_double2(sx / (double)n_used, sy / (double)n_used);
+  part[g][lane] = make_double2(sx, sy);
+  __syncthreads();
+  if (g == 0 && valid) {
+#pragma unroll
+    for (int r = 1; r < kMeanGroups; ++r) {
+      sx += part[r][lane].x;
+      sy += part[r][lane].y;
+    }
+    out[(int64_t)(probe0 + i) * n_k + k] = make_double2(sx / (double)n_used, sy / (double)n_used);
+  }
 }
 
 hipError_t launch_mean_exact(const void* in, int in_dtype, int64_t pstride, int64_t fstride,
                              int32_t nx, int64_t rs, int64_t n_used, int32_t probe0,
                              int32_t n_probes, int32_t n_k, double2* mu, hipStream_t st) {
-  dim3 g((n_k + 255) / 256, n_probes);
+  dim3 g((n_k + 63) / 64, n_probes);
+  const dim3 b(64 * kMeanGroups);
   if (in_dtype == 1)
-    hipLaunchKernelGGL(mean_kernel<double2>, g, dim3(256), 0, st, (const double2*)in, pstride,
-                       fstride, nx, rs, n_used, probe0, n_probes, n_k, mu);
+    hipLaunchKernelGGL(mean_kernel<double2>, g, b, 0, st, (const double2*)in, pstride, fstride, nx,
+                       rs, n_used, probe0, n_probes, n_k, mu);
   else
-    hipLaunchKernelGGL(mean_kernel<float2>, g, dim3(256), 0, st, (const float2*)in, pstride,
-                       fstride, nx, rs, n_used, probe0, n_probes, n_k, mu);
+    hipLaunchKernelGGL(mean_kernel<float2>, g, b, 0, st, (const float2*)in, pstride, fstride, nx,
+                       rs, n_used, probe0, n_probes, n_k, mu);
   return hipGetLastError();
 }
 
