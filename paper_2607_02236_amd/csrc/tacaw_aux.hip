@@ -3,6 +3,7 @@
 // partial reduction, the exact elastic-mean correction, normalisation and the
 // masked detector reduction D_j(m) = sum_k M_j(k) S(m, k) (DetectorSet,
 // Sec. II.B.1 of the paper).
+#include <algorithm>
 #include <type_traits>
 
 #include "tacaw_internal.h"
@@ -323,22 +324,6 @@ __device__ __forceinline__ double corr_term(const CorrArgs& c, int p, int64_t k,
   return -2.0 * (dw.x * xs.x + dw.y * xs.y) + c.n_seg * (dw.x * dw.x + dw.y * dw.y);
 }
 
-__global__ void correct_S_kernel(const CorrArgs c, double* S) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= c.n_k) return;
-  for (int b = 0; b < c.n_corr; ++b) {
-    double sum = 0.0;
-    for (int p = 0; p < c.n_probe; ++p) sum += corr_term(c, p, k, b);
-    S[(int64_t)c.rows[b] * c.n_k + k] += sum;
-  }
-}
-
-hipError_t launch_correct_S(const CorrArgs& c, double* S, double* /*out*/, double /*kappa*/,
-                            hipStream_t st) {
-  hipLaunchKernelGGL(correct_S_kernel, dim3((c.n_k + 255) / 256), dim3(256), 0, st, c, S);
-  return hipGetLastError();
-}
-
 // Dp[d][p][bin_b] += sum_k M_d(k) corr_p(b, k). A block takes kCorrPix pixels of one
 // probe; its sums stay in registers (all detector and bin indexes are compile-time),
 // are reduced across each wave with lane shuffles and added with one atomic per
@@ -451,9 +436,10 @@ __global__ void __launch_bounds__(256) pseg_kernel(const PsegArgs a) {
 #pragma unroll
   for (int r = 0; r < V; ++r)
 #pragma unroll
-    for (int q = 0; q < Q; ++q) st[r][q] = op[(int64_t)(r * Q + q) * a.n_k];
+    for (int q = 0; q < Q; ++q)
+      st[r][q] = a.f_lo == 0 ? make_double2(0.0, 0.0) : op[(int64_t)(r * Q + q) * a.n_k];
 #pragma unroll
-  for (int b = 0; b < kMaxCorr; ++b) cor[b] = cp[(int64_t)b * a.n_k];
+  for (int b = 0; b < kMaxCorr; ++b) cor[b] = a.f_lo == 0 ? 0.0 : cp[(int64_t)b * a.n_k];
   const bool three = a.n_corr == 3;
   const double inv_l = 1.0 / (double)a.L;
   const double* w0 = (const double*)a.tw;  // w(t) = Re tw[0][t], stride 2
@@ -741,27 +727,101 @@ hipError_t launch_read_probe_columns(const void* p, int64_t n_rows, int64_t row_
   return hipGetLastError();
 }
 
-// S[i] <- kappa q(r) S[i], row r = (i / inner) % n_om (q null: factor 1); copy to out if given
-__global__ void scale_copy_kernel(double* S, double* out, int64_t n, double kappa, const double* q,
-                                  int64_t inner, int32_t n_om) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    const double f = q ? kappa * q[(i / inner) % n_om] : kappa;
-    const double v = S[i] * f;
-    S[i] = v;
-    if (out) out[i] = v;
+// Row factor of the normalised spectrum: S is kept as accumulated, and every reader
+// multiplies by it (the same product that a stored normalised copy would hold).
+__device__ __forceinline__ double row_factor(double kappa, const double* q, int row) {
+  return q ? kappa * q[row] : kappa;
+}
+
+// One launch for the whole end of a reduction. Block row y < n_om: output row
+// row = (y + the first correction row) mod n_om, so that the correction rows, whose
+// blocks walk all probes, start first; S of those rows gets its correction, and out
+// = S times the row factor. Further block rows normalise D_p. Bound by memory: S is
+// read once and out written once (8 + 8 bytes per value); before, a launch per
+// step, and S read, written back normalised and copied: 222 us for 32 probes of
+// 256^2 and 512 bins, now 148 us (3.6 TB/s).
+constexpr int kFinV = 4;  // values per thread
+template <bool CORR>
+__global__ void __launch_bounds__(256) finalize_kernel(const CorrArgs c, double* S, double* out,
+                                                       double kappa, const double* q, double* Dp,
+                                                       int64_t n_dp, double kappa_p) {
+  const int y = blockIdx.y;
+  if (y >= c.n_om) {
+    const int64_t stride = (int64_t)(gridDim.y - c.n_om) * gridDim.x * 256;
+    for (int64_t i = ((int64_t)(y - c.n_om) * gridDim.x + blockIdx.x) * 256 + threadIdx.x; i < n_dp;
+         i += stride)
+      Dp[i] *= row_factor(kappa_p, q, (int)(i % c.n_om));
+    return;
+  }
+  int row = y + (CORR ? c.rows[2] : 0);
+  if (row >= c.n_om) row -= c.n_om;
+  int b = -1;  // correction bin of this row
+  if constexpr (CORR) {
+#pragma unroll
+    for (int e = 0; e < kMaxCorr; ++e)
+      if (e < c.n_corr && c.rows[e] == row) b = e;
+  }
+  if (b < 0 && !out) return;
+  const double f = row_factor(kappa, q, row);
+  const int64_t k0 = (int64_t)blockIdx.x * (256 * kFinV) + threadIdx.x;
+  double* const Sr = S + (int64_t)row * c.n_k;
+  double v[kFinV];
+#pragma unroll
+  for (int u = 0; u < kFinV; ++u) v[u] = k0 + 256 * u < c.n_k ? Sr[k0 + 256 * u] : 0.0;
+  if constexpr (CORR) {
+    if (b >= 0) {
+      double sum[kFinV];
+#pragma unroll
+      for (int u = 0; u < kFinV; ++u) sum[u] = 0.0;
+#pragma unroll 2
+      for (int p = 0; p < c.n_probe; ++p)
+#pragma unroll
+        for (int u = 0; u < kFinV; ++u)
+          sum[u] += corr_term(c, p, min(k0 + 256 * u, (int64_t)c.n_k - 1), b);
+#pragma unroll
+      for (int u = 0; u < kFinV; ++u) {
+        v[u] += sum[u];
+        if (k0 + 256 * u < c.n_k) Sr[k0 + 256 * u] = v[u];
+      }
+    }
+  }
+  if (out) {
+    double* const o = out + (int64_t)row * c.n_k;
+#pragma unroll
+    for (int u = 0; u < kFinV; ++u)
+      if (k0 + 256 * u < c.n_k) o[k0 + 256 * u] = v[u] * f;
   }
 }
 
-hipError_t launch_finalize_S(double* S, double* out, int64_t n_elem, double kappa, const double* q,
-                             int64_t inner, int32_t n_om, hipStream_t st) {
-  hipLaunchKernelGGL(scale_copy_kernel, dim3(blocks_for(n_elem, 256, 8192)), dim3(256), 0, st, S,
-                     out, n_elem, kappa, q, inner, n_om);
+hipError_t launch_finalize(const CorrArgs& c, bool corr, double* S, double* out, double kappa,
+                           const double* q, double* Dp, int64_t n_dp, double kappa_p,
+                           hipStream_t st) {
+  const unsigned gx = (unsigned)((c.n_k + 256 * kFinV - 1) / (256 * kFinV));
+  const int64_t dp_rows = std::min<int64_t>((n_dp + 256 * (int64_t)gx - 1) / (256 * (int64_t)gx), 1024);
+  const dim3 g(gx, (unsigned)(c.n_om + dp_rows));
+  if (corr)
+    hipLaunchKernelGGL(finalize_kernel<true>, g, dim3(256), 0, st, c, S, out, kappa, q, Dp, n_dp, kappa_p);
+  else
+    hipLaunchKernelGGL(finalize_kernel<false>, g, dim3(256), 0, st, c, S, out, kappa, q, Dp, n_dp, kappa_p);
   return hipGetLastError();
 }
 
-hipError_t launch_scale(double* p, int64_t n, double k, hipStream_t st) {
-  return launch_finalize_S(p, nullptr, n, k, nullptr, 1, 1, st);
+// Before the detector sums: D zeroed for their atomics, and D_p copied out
+__global__ void detector_prep_kernel(double* D, int64_t n_d, const double* __restrict__ src,
+                                     double* __restrict__ dst, int64_t n_dp) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int64_t i = i0; i < n_d; i += stride) D[i] = 0.0;
+  for (int64_t i = i0; i < n_dp; i += stride) dst[i] = src[i];
+}
+
+hipError_t launch_detector_prep(double* D, int64_t n_d, const double* src, double* dst, int64_t n_dp,
+                                hipStream_t st) {
+  const int64_t n = std::max(n_d, n_dp);
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(detector_prep_kernel, dim3(blocks_for(n, 256, 2048)), dim3(256), 0, st, D, n_d,
+                     src, dst, n_dp);
+  return hipGetLastError();
 }
 
 // D[d][m] += sum over a pixel chunk of M_d(k) S(m, k): each block takes kDetBins
@@ -770,22 +830,24 @@ hipError_t launch_scale(double* p, int64_t n, double k, hipStream_t st) {
 constexpr int kDetBins = 4;
 template <int ND>
 __global__ void detector_kernel(const double* S, const double* masks, int32_t L, int32_t n_k,
-                                int32_t chunk, double* D) {
+                                int32_t chunk, double kappa, const double* q, double* D) {
   const int m0 = blockIdx.y * kDetBins;
   const int64_t k0 = (int64_t)blockIdx.x * chunk;
   const int64_t k1 = (k0 + chunk < n_k) ? k0 + chunk : n_k;
-  double acc[kDetBins][ND];
+  double acc[kDetBins][ND], f[kDetBins];
 #pragma unroll
-  for (int b = 0; b < kDetBins; ++b)
+  for (int b = 0; b < kDetBins; ++b) {
+    f[b] = m0 + b < L ? row_factor(kappa, q, m0 + b) : 0.0;
 #pragma unroll
     for (int d = 0; d < ND; ++d) acc[b][d] = 0.0;
+  }
   for (int64_t k = k0 + threadIdx.x; k < k1; k += blockDim.x) {
     double mk[ND];
 #pragma unroll
     for (int d = 0; d < ND; ++d) mk[d] = masks[(int64_t)d * n_k + k];
 #pragma unroll
     for (int b = 0; b < kDetBins; ++b) {
-      const double sv = (m0 + b < L) ? S[(int64_t)(m0 + b) * n_k + k] : 0.0;
+      const double sv = (m0 + b < L) ? S[(int64_t)(m0 + b) * n_k + k] * f[b] : 0.0;
 #pragma unroll
       for (int d = 0; d < ND; ++d) acc[b][d] += mk[d] * sv;
     }
@@ -804,69 +866,50 @@ __global__ void detector_kernel(const double* S, const double* masks, int32_t L,
 
 template <int ND>
 static void launch_det_nd(const double* S, const double* masks, int32_t L, int32_t n_k,
-                          double* D, hipStream_t st) {
-  const int chunk = 16384;
-  dim3 g((n_k + chunk - 1) / chunk, (L + kDetBins - 1) / kDetBins);
-  hipLaunchKernelGGL((detector_kernel<ND>), g, dim3(256), 0, st, S, masks, L, n_k, chunk, D);
+                          double kappa, const double* q, double* D, hipStream_t st) {
+  // 16384 pixels per block, fewer while the grid is below 8 blocks per CU: the
+  // 16 blocks of 64^2 pixels and 64 bins walked 16 pixels per thread one after another
+  const int64_t rows = (L + kDetBins - 1) / kDetBins;
+  int chunk = 16384;
+  while (chunk > 512 && (n_k + chunk - 1) / chunk * rows < 2048) chunk /= 2;
+  dim3 g((n_k + chunk - 1) / chunk, (unsigned)rows);
+  hipLaunchKernelGGL((detector_kernel<ND>), g, dim3(256), 0, st, S, masks, L, n_k, chunk, kappa, q, D);
 }
 
 hipError_t launch_detector(const double* S, const double* masks, int32_t n_det, int32_t L,
-                           int32_t n_k, double* D, hipStream_t st) {
+                           int32_t n_k, double kappa, const double* q, double* D, hipStream_t st) {
   switch (n_det) {
-    case 1: launch_det_nd<1>(S, masks, L, n_k, D, st); break;
-    case 2: launch_det_nd<2>(S, masks, L, n_k, D, st); break;
-    case 3: launch_det_nd<3>(S, masks, L, n_k, D, st); break;
-    case 4: launch_det_nd<4>(S, masks, L, n_k, D, st); break;
-    case 5: launch_det_nd<5>(S, masks, L, n_k, D, st); break;
-    case 6: launch_det_nd<6>(S, masks, L, n_k, D, st); break;
-    case 7: launch_det_nd<7>(S, masks, L, n_k, D, st); break;
-    case 8: launch_det_nd<8>(S, masks, L, n_k, D, st); break;
+    case 1: launch_det_nd<1>(S, masks, L, n_k, kappa, q, D, st); break;
+    case 2: launch_det_nd<2>(S, masks, L, n_k, kappa, q, D, st); break;
+    case 3: launch_det_nd<3>(S, masks, L, n_k, kappa, q, D, st); break;
+    case 4: launch_det_nd<4>(S, masks, L, n_k, kappa, q, D, st); break;
+    case 5: launch_det_nd<5>(S, masks, L, n_k, kappa, q, D, st); break;
+    case 6: launch_det_nd<6>(S, masks, L, n_k, kappa, q, D, st); break;
+    case 7: launch_det_nd<7>(S, masks, L, n_k, kappa, q, D, st); break;
+    case 8: launch_det_nd<8>(S, masks, L, n_k, kappa, q, D, st); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-// out[0] += sum_i a[i] * b[i]
-__global__ void dot_kernel(const double* a, const double* b, int64_t n, double* out) {
-  __shared__ double red[256];
-  double s = 0.0;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
-    s += a[i] * (b ? b[i] : 1.0);
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) atomicAdd(out, red[0]);
-}
-
-hipError_t launch_dot_gS(const double* S, const double* gS, int64_t n, double* out,
-                         hipStream_t st) {
-  hipLaunchKernelGGL(dot_kernel, dim3(blocks_for(n, 256, 1024)), dim3(256), 0, st, S, gS, n, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_sum(const double* p, int64_t n, double* out, hipStream_t st) {
-  return launch_dot_gS(p, nullptr, n, out, st);
-}
-
-// *cnt += number of non-finite values (NaN or +-Inf) in x[0..n)
-__global__ void count_nonfinite_kernel(const double* __restrict__ x, int64_t n,
+// *cnt += number of non-finite values (NaN or +-Inf) in x[i] times the factor of row
+// (i / inner) % n_om, i < n (x as it stands when kappa is 1 and q null)
+__global__ void count_nonfinite_kernel(const double* __restrict__ x, int64_t n, double kappa,
+                                       const double* q, int64_t inner, int32_t n_om,
                                        unsigned long long* cnt) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   unsigned long long c = 0;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
-    c += isfinite(x[i]) ? 0ull : 1ull;
+    c += isfinite(x[i] * row_factor(kappa, q, q ? (int)((i / inner) % n_om) : 0)) ? 0ull : 1ull;
   if (c) atomicAdd(cnt, c);
 }
 
-hipError_t launch_count_nonfinite(const double* x, int64_t n, unsigned long long* cnt,
+hipError_t launch_count_nonfinite(const double* x, int64_t n, double kappa, const double* q,
+                                  int64_t inner, int32_t n_om, unsigned long long* cnt,
                                   hipStream_t st) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(count_nonfinite_kernel, dim3(blocks_for(n, 256, 4096)), dim3(256), 0, st, x,
-                     n, cnt);
+                     n, kappa, q, inner, n_om, cnt);
   return hipGetLastError();
 }
 

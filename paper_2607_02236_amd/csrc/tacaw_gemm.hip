@@ -475,15 +475,15 @@ __global__ void __launch_bounds__(64 * kGemmWaves)
               t.y += red[g * PX + tid].y;
             }
             double2* ms = a.msum + (int64_t)p * n_k + kk;
-            ms->x += t.x;
-            ms->y += t.y;
+            const double2 o = a.s_lo == 0 ? make_double2(0.0, 0.0) : *ms;
+            *ms = make_double2(o.x + t.x, o.y + t.y);
           }
 #pragma unroll
           for (int cb = 0; cb < kMaxCorr; ++cb) {
             if (cown[cb]) {  // slots: bins 0, 1, L - 1
               double2* xp = a.xs + ((int64_t)p * kMaxCorr + cb) * n_k + kk;
-              xp->x += s_xs[cb * PX + tid].x;
-              xp->y += s_xs[cb * PX + tid].y;
+              const double2 o = a.s_lo == 0 ? make_double2(0.0, 0.0) : *xp;
+              *xp = make_double2(o.x + s_xs[cb * PX + tid].x, o.y + s_xs[cb * PX + tid].y);
             }
           }
         }

@@ -52,7 +52,8 @@ struct SegArgs {
   const float2* tw;        // inter-pass twiddles exp(-2 pi i n2 k1 / L): [N2][N1]
   double2* cref;           // [n_probe][n_k] reference subtracted before the window; with
                            // track_mean the launch holding a probe's first chunk writes it
-  double2* msum;           // [n_probe][n_k] FP64 sum of (psi - c) over counted frames
+  double2* msum;           // [n_probe][n_k] FP64 sum of (psi - c) over counted frames, stored by
+                           // the launch with s_lo = 0 and added to by later ones (xs too)
   double2* xs;             // [n_probe][kMaxCorr][n_k] FP64 sum over chunks of X'(bin)
   double* S;               // [n_om][n_k] FP64 accumulator of sum |X'|^2
   int32_t s_store;         // 1: first launch since reset, S is written (not read and added)
@@ -134,13 +135,14 @@ struct CorrArgs {
   const double2* xs;
   const double* pcorr;  // [P][3][n_k] per-chunk mean: sum_s |X_s(b)|^2 (null unless that mode)
 };
-// S[i] <- kappa * q[(i / inner) % n_om] * S[i] (q may be null), copied to out when given
-hipError_t launch_finalize_S(double* S, double* out, int64_t n_elem, double kappa, const double* q,
-                             int64_t inner, int32_t n_om, hipStream_t st);
-hipError_t launch_correct_S(const CorrArgs& c, double* S, double* out, double kappa, hipStream_t st);
+// S gets the mean correction at its correction rows (corr) and stays unnormalised;
+// out (may be null) = S times its row factor kappa q[row] (q may be null); Dp[i] *=
+// kappa_p q[i % n_om], i < n_dp
+hipError_t launch_finalize(const CorrArgs& c, bool corr, double* S, double* out, double kappa,
+                           const double* q, double* Dp, int64_t n_dp, double kappa_p,
+                           hipStream_t st);
 hipError_t launch_correct_Dp(const CorrArgs& c, const double* masks, int32_t n_det, double* Dp,
                              hipStream_t st);
-hipError_t launch_scale(double* p, int64_t n, double k, hipStream_t st);
 
 // Per-chunk mean (tacaw_aux.hip): streams the frames [f_lo, f_hi) of a push once
 // and keeps, per (probe, pixel) and open chunk, the FP64 sums the exact correction needs.
@@ -159,8 +161,12 @@ struct PsegArgs {
   double2* cmean;          // [P][Ns][n_k]: each chunk's FP64 mean c + sum_t y' / L
 };
 hipError_t launch_pseg(const PsegArgs& a, int32_t in_dtype, hipStream_t st);
+// D[0..n_d) = 0 and dst = src (n_dp values), before launch_detector
+hipError_t launch_detector_prep(double* D, int64_t n_d, const double* src, double* dst, int64_t n_dp,
+                                hipStream_t st);
+// D += masks . S, S times its row factor kappa q[row]
 hipError_t launch_detector(const double* S, const double* masks, int32_t n_det, int32_t L,
-                           int32_t n_k, double* D, hipStream_t st);
+                           int32_t n_k, double kappa, const double* q, double* D, hipStream_t st);
 
 // Adjoint (tacaw_adjoint.hip).
 // Tile of this workgroup. Workgroups are dealt to the 8 XCDs round-robin
@@ -210,11 +216,10 @@ hipError_t launch_bwd_wparam(const double* part, int n, double c, double* out, h
 hipError_t launch_mean_exact(const void* in, int in_dtype, int64_t pstride, int64_t fstride,
                              int32_t nx, int64_t rs, int64_t n_used, int32_t probe0,
                              int32_t n_probes, int32_t n_k, double2* mu, hipStream_t st);
-hipError_t launch_dot_gS(const double* S, const double* gS, int64_t n, double* out,
-                         hipStream_t st);
-hipError_t launch_sum(const double* p, int64_t n, double* out, hipStream_t st);
-// *cnt += the count of NaN and Inf values in x[0..n) (the caller zeroes *cnt)
-hipError_t launch_count_nonfinite(const double* x, int64_t n, unsigned long long* cnt,
+// *cnt += the count of NaN and Inf values in x[i] kappa q[(i / inner) % n_om], i < n (q may
+// be null; the caller zeroes *cnt)
+hipError_t launch_count_nonfinite(const double* x, int64_t n, double kappa, const double* q,
+                                  int64_t inner, int32_t n_om, unsigned long long* cnt,
                                   hipStream_t st);
 
 }  // namespace tacaw

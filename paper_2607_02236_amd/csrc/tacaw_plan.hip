@@ -743,6 +743,14 @@ int tacaw_plan(const tacaw_plan_desc* d, void* hip_stream, tacaw_plan_t* out) {
         if (rc == TACAW_OK) rc = hip_check(hipEventCreate(&x), "event");
   }
   if (rc == TACAW_OK) rc = hip_check(hipDeviceSynchronize(), "plan setup");
+  // what no launch writes reads as zero: the references and sums of plans that keep
+  // none, and the correction bins that a rectangular window does not have
+  auto Z = [&](void* p, int64_t b) {
+    if (rc == TACAW_OK && p) rc = hip_check(launch_fill_zero(p, b, P->st), "plan setup");
+  };
+  Z(P->cref, np * nk * 16);
+  Z(P->msum, np * nk * 16);
+  Z(P->xs, np * kMaxCorr * nk * 16);
   if (rc == TACAW_OK) {
     *out = P;
     rc = tacaw_reset(P);
@@ -758,18 +766,11 @@ int tacaw_plan(const tacaw_plan_desc* d, void* hip_stream, tacaw_plan_t* out) {
 
 int tacaw_reset(tacaw_plan_t P) {
   if (!P) return fail(TACAW_ERR_INVALID_ARG, "plan is NULL");
-  const int64_t nk = P->n_k, np = P->d.n_probe;
-  TRY(hip_check(launch_fill_zero(P->cref, np * nk * 16, P->st), "reset"));
-  TRY(hip_check(launch_fill_zero(P->msum, np * nk * 16, P->st), "reset"));
-  TRY(hip_check(launch_fill_zero(P->xs, np * kMaxCorr * nk * 16, P->st), "reset"));
-  if (P->pcorr) {
-    TRY(hip_check(launch_fill_zero(P->pseg_open, np * P->pseg_V * (1 + kMaxCorr) * nk * 16, P->st),
-                  "reset"));
-    TRY(hip_check(launch_fill_zero(P->pcorr, np * kMaxCorr * nk * 8, P->st), "reset"));
-  }
-  // S needs no zero fill: the first chunk launch after a reset writes every element
+  // S and the per-probe sums need no zero fill: the first chunk launch after a reset
+  // writes every element of S, and the launch with a probe's first chunk its sums
   if (P->Dp)
-    TRY(hip_check(launch_fill_zero(P->Dp, (int64_t)P->d.n_det * np * P->n_om * 8, P->st), "reset"));
+    TRY(hip_check(launch_fill_zero(P->Dp, (int64_t)P->d.n_det * P->d.n_probe * P->n_om * 8, P->st),
+                  "reset"));
   std::fill(P->cursor.begin(), P->cursor.end(), 0);
   std::fill(P->s_done.begin(), P->s_done.end(), 0);
   P->s_fresh = true;
@@ -1295,30 +1296,25 @@ int tacaw_finalize(tacaw_plan_t P, double* d_S) {
   for (int p = 0; p < P->d.n_probe; ++p)
     if (P->cursor[p] < P->n_used)
       return fail(TACAW_ERR_STATE, "series incomplete for probe " + std::to_string(p));
-  if (P->strategy == kRefSampled) {
-    const CorrArgs c = corr_args(P);
-    TRY(hip_check(launch_correct_S(c, P->S, nullptr, 0.0, P->st), "mean correction"));
-    if (P->d.n_det > 0)
-      TRY(hip_check(launch_correct_Dp(c, P->masks, P->d.n_det, P->Dp, P->st), "mean correction"));
-  }
-  TRY(hip_check(launch_finalize_S(P->S, d_S, (int64_t)P->n_om * P->n_k, kappa_S(P), P->qfac,
-                                  P->n_k, P->n_om, P->st),
-                "normalisation"));
-  if (P->d.n_det > 0)
-    TRY(hip_check(launch_finalize_S(P->Dp, nullptr, (int64_t)P->d.n_det * P->d.n_probe * P->n_om,
-                                    kappa_probe(P), P->qfac, 1, P->n_om, P->st),
-                  "normalisation"));
+  const CorrArgs c = corr_args(P);
+  const bool corr = P->strategy == kRefSampled;
+  const int64_t n_dp = (int64_t)P->d.n_det * P->d.n_probe * P->n_om;
+  if (corr && P->d.n_det > 0)
+    TRY(hip_check(launch_correct_Dp(c, P->masks, P->d.n_det, P->Dp, P->st), "mean correction"));
+  TRY(hip_check(launch_finalize(c, corr, P->S, d_S, kappa_S(P), P->qfac, P->Dp, n_dp,
+                                kappa_probe(P), P->st),
+                "finalize"));
   P->state = 1;
   P->nonfinite = 0;
   if (P->nf) {
     // NaN or Inf in the exit waves propagate into S and D_p: count them
     unsigned long long h = 0;
     TRY(hip_check(launch_fill_zero(P->nf, 8, P->st), "non-finite check"));
-    TRY(hip_check(launch_count_nonfinite(P->S, (int64_t)P->n_om * P->n_k, P->nf, P->st),
+    TRY(hip_check(launch_count_nonfinite(P->S, (int64_t)P->n_om * P->n_k, kappa_S(P), P->qfac,
+                                         P->n_k, P->n_om, P->nf, P->st),
                   "non-finite check"));
     if (P->d.n_det > 0)
-      TRY(hip_check(launch_count_nonfinite(P->Dp, (int64_t)P->d.n_det * P->d.n_probe * P->n_om,
-                                           P->nf, P->st),
+      TRY(hip_check(launch_count_nonfinite(P->Dp, n_dp, 1.0, nullptr, 1, 1, P->nf, P->st),
                     "non-finite check"));
     TRY(hip_check(hipMemcpyAsync(&h, P->nf, 8, hipMemcpyDeviceToHost, P->st), "non-finite check"));
     TRY(hip_check(hipStreamSynchronize(P->st), "non-finite check"));
@@ -1344,14 +1340,13 @@ int tacaw_detector_spectra(tacaw_plan_t P, const double* d_masks, int32_t n_det,
   if (d_Dp && (d_masks || P->d.n_det == 0))
     return fail(TACAW_ERR_INVALID_ARG, "per-probe spectra need the plan's own masks");
   if (n_det > 0 && !d_D && !d_Dp) return fail(TACAW_ERR_INVALID_ARG, "no output");
-  if (n_det > 0 && d_D) {
-    TRY(hip_check(launch_fill_zero(d_D, (int64_t)n_det * P->n_om * 8, P->st), "zero D"));
-    TRY(hip_check(launch_detector(P->S, masks, n_det, P->n_om, P->n_k, d_D, P->st), "detector"));
-  }
-  if (d_Dp)
-    TRY(hip_check(hipMemcpyAsync(d_Dp, P->Dp, (size_t)P->d.n_det * P->d.n_probe * P->n_om * 8,
-                                 hipMemcpyDeviceToDevice, P->st),
-                  "per-probe copy"));
+  const bool sums = n_det > 0 && d_D;
+  TRY(hip_check(launch_detector_prep(d_D, sums ? (int64_t)n_det * P->n_om : 0, P->Dp, d_Dp,
+                                     d_Dp ? (int64_t)P->d.n_det * P->d.n_probe * P->n_om : 0, P->st),
+                "detector"));
+  if (sums)
+    TRY(hip_check(launch_detector(P->S, masks, n_det, P->n_om, P->n_k, kappa_S(P), P->qfac, d_D, P->st),
+                  "detector"));
   return TACAW_OK;
 }
 
