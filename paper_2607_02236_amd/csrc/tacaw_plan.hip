@@ -114,19 +114,30 @@ float f16_value(uint16_t b) {
   return (float)h;
 }
 
+// cos and sin of -2 pi q / L, q < L: every angle of the L-point DFT. (Calling them
+// for all L^2 products took most of a plan's creation: 5.5 ms at L = 512.)
+std::vector<double2> make_trig(int L) {
+  std::vector<double2> tr(L);
+  for (int q = 0; q < L; ++q) {
+    const double ang = -kTwoPi * (double)q / L;
+    tr[q] = make_double2(std::cos(ang), std::sin(ang));
+  }
+  return tr;
+}
+
 // Window-folded DFT matrix of the GEMM form as hi and lo 16-bit parts:
 // [2][m_rows][2L], row 2r + c (c: 0 real, 1 imaginary part of output row r, which
 // holds bin m = (r - roi_half) mod L), column 2t + c' (c' multiplies Re or Im of
 // frame t): [[Fr, -Fi], [Fi, Fr]] interleaved; rows from 2 n_om on are zero.
-std::vector<uint16_t> make_dft_matrix(const std::vector<double>& w, bool fp16, int n_om,
-                                      int roi_half, int m_rows) {
+std::vector<uint16_t> make_dft_matrix(const std::vector<double>& w, const std::vector<double2>& tr,
+                                      bool fp16, int n_om, int roi_half, int m_rows) {
   const int L = (int)w.size(), K2 = 2 * L;
   std::vector<uint16_t> out((size_t)2 * m_rows * K2, 0);
   for (int r = 0; r < n_om; ++r) {
     const int m = (r - roi_half + L) % L;
     for (int t = 0; t < L; ++t) {
-      const double ang = -6.283185307179586476925286766559 * (double)(((int64_t)m * t) % L) / L;
-      const double fr = w[t] * std::cos(ang), fi = w[t] * std::sin(ang);
+      const double2 e0 = tr[((int64_t)m * t) % L];
+      const double fr = w[t] * e0.x, fi = w[t] * e0.y;
       const double e[2][2] = {{fr, -fi}, {fi, fr}};
       for (int c = 0; c < 2; ++c) {
         for (int cp = 0; cp < 2; ++cp) {
@@ -163,7 +174,7 @@ struct tacaw_plan_s {
   int L = 0, H = 0, Ns = 0, n_k = 0, N1 = 0, N2 = 0, W = 0, n_tiles = 0;
   int n_om = 0, roi = 0, m_rows = 0;  // output rows, energy window M, GEMM rows
   int64_t n_used = 0;
-  double sumw2 = 0.0;
+  double sumw2 = 0.0, sum_wdw = 0.0;  // sum_t w(t)^2, sum_t w(t) dw(t)/dr
   int n_corr = 0;
   int bins[kMaxCorr] = {0, 0, 0};  // correction bins 0, 1, L-1 and their output rows
   int rows[kMaxCorr] = {0, 0, 0};
@@ -181,7 +192,10 @@ struct tacaw_plan_s {
   std::vector<int> slot_owner;
   std::vector<std::pair<void**, int64_t>> owned;
   int64_t bytes = 0;
-  // device buffers
+  std::vector<char> upload;     // host side of the tables' copy
+  std::vector<int32_t> slots;   // host side of pair_slot
+  // device buffers (arena: one allocation that holds those made with the plan)
+  void* arena = nullptr;
   float* win_t = nullptr;   // [N2][N1]
   float* dwin_t = nullptr;  // [N2][N1] (HANN_WIDTH)
   float2* tw = nullptr;     // [N2][N1]
@@ -202,7 +216,7 @@ struct tacaw_plan_s {
   int64_t dpart_bytes = 0;
   void* ring = nullptr;
   void* fmat = nullptr;     // DFT-GEMM operand (GEMM transforms)
-  double* scratch = nullptr;
+  double* scratch = nullptr;  // adjoint workspace, made by the first tacaw_backward
   int64_t scratch_bytes = 0;
   float* gscale = nullptr;  // GEMM form: [P][n_k]
   double* qfac = nullptr;   // [n_om] quantum-statistics factor per row (temperature > 0)
@@ -577,13 +591,15 @@ int tacaw_plan(const tacaw_plan_desc* d, void* hip_stream, tacaw_plan_t* out) {
     delete P;
     return fail(TACAW_ERR_INVALID_ARG, "window is identically zero");
   }
+  const std::vector<double2> tr = make_trig(P->L);
   std::vector<double2> Wm(P->L);
   for (int m = 0; m < P->L; ++m) {
     double re = 0.0, im = 0.0;
-    for (int t = 0; t < P->L; ++t) {
-      const double ang = -kTwoPi * (double)(((int64_t)m * t) % P->L) / P->L;
-      re += w[t] * std::cos(ang);
-      im += w[t] * std::sin(ang);
+    for (int t = 0, q = 0; t < P->L; ++t) {  // q = m t mod L
+      re += w[t] * tr[q].x;
+      im += w[t] * tr[q].y;
+      q += m;
+      if (q >= P->L) q -= P->L;
     }
     Wm[m] = make_double2(re, im);
   }
@@ -626,74 +642,87 @@ int tacaw_plan(const tacaw_plan_desc* d, void* hip_stream, tacaw_plan_t* out) {
   const std::vector<double> dw =
       d->window == TACAW_WIN_HANN_WIDTH ? make_window_dr(P->L, d->window_param)
                                         : std::vector<double>(P->L, 0.0);
+  for (int t = 0; t < P->L; ++t) P->sum_wdw += w[t] * dw[t];
   for (int n2 = 0; n2 < P->N2; ++n2) {
     for (int n1 = 0; n1 < P->N1; ++n1) {
       const int t = P->N2 * n1 + n2;
       wt[n2 * P->N1 + n1] = (float)w[t];
       dwt[n2 * P->N1 + n1] = (float)dw[t];
       const int k1 = n1;
-      const double ang = -kTwoPi * (double)(((int64_t)n2 * k1) % P->L) / P->L;
-      twt[n2 * P->N1 + k1] = make_float2((float)std::cos(ang), (float)std::sin(ang));
+      const double2 e = tr[(n2 * k1) % P->L];
+      twt[n2 * P->N1 + k1] = make_float2((float)e.x, (float)e.y);
     }
   }
 
-  int rc = TACAW_OK;
-  auto A = [&](void** p, int64_t b, const char* what) {
-    if (rc == TACAW_OK) rc = P->alloc(p, b, what);
-  };
   if (hipGetDevice(&P->device) != hipSuccess) {
     (void)hipGetLastError();
     delete P;
     return fail(TACAW_ERR_HIP, "no HIP device available");
   }
+  // The plan's buffers are parts of one allocation, and its tables go up in one copy
+  // on its stream (an allocation, a free or a blocking copy each costs ten
+  // microseconds or more, and a one-shot call pays for all of them).
   const int64_t nk = P->n_k, np = d->n_probe;
-  A((void**)&P->win_t, P->L * 4, "window");
-  A((void**)&P->dwin_t, P->L * 4, "window derivative");
-  A((void**)&P->tw, P->L * 8, "twiddles");
-  A((void**)&P->cref, np * nk * 16, "references");
-  A((void**)&P->msum, np * nk * 16, "mean sums");
-  A((void**)&P->xs, np * kMaxCorr * nk * 16, "correction sums");
-  A((void**)&P->S, (int64_t)P->n_om * nk * 8, "spectrum accumulator");
-  if (d->flags & TACAW_FLAG_CHECK_FINITE) A((void**)&P->nf, 8, "non-finite count");
+  struct Part {
+    void** p;
+    int64_t bytes, off;
+  };
+  std::vector<Part> parts;
+  int64_t total = 0;
+  auto A = [&](void** p, int64_t b) {
+    parts.push_back({p, b, total});
+    total += (b + 255) / 256 * 256;
+  };
+  // tables first: one contiguous upload
+  A((void**)&P->win_t, P->L * 4);
+  A((void**)&P->dwin_t, P->L * 4);
+  A((void**)&P->tw, P->L * 8);
+  if (d->mean_mode == TACAW_MEAN_PER_SEGMENT) A((void**)&P->pseg_tw, (int64_t)kMaxCorr * P->L * 16);
+  if (d->temperature_K > 0.0) A((void**)&P->qfac, (int64_t)P->n_om * 8);
+  if (gemm) A(&P->fmat, (int64_t)2 * P->m_rows * (2 * P->L) * 2);
+  const int64_t table_bytes = total;
+  A((void**)&P->cref, np * nk * 16);
+  A((void**)&P->msum, np * nk * 16);
+  A((void**)&P->xs, np * kMaxCorr * nk * 16);
+  const int64_t zero_end = total;  // cref, msum and xs start as zeros
+  A((void**)&P->S, (int64_t)P->n_om * nk * 8);
+  if (d->flags & TACAW_FLAG_CHECK_FINITE) A((void**)&P->nf, 8);
   if (d->mean_mode == TACAW_MEAN_PER_SEGMENT) {
     P->pseg_V = (P->L + P->H - 1) / P->H;
-    A((void**)&P->pseg_tw, (int64_t)kMaxCorr * P->L * 16, "per-chunk mean twiddles");
-    A((void**)&P->pseg_open, np * P->pseg_V * (1 + kMaxCorr) * nk * 16, "open chunk sums");
-    A((void**)&P->pcorr, np * kMaxCorr * nk * 8, "per-chunk mean corrections");
-    A((void**)&P->pref, np * nk * 16, "per-chunk mean references");
-    A((void**)&P->cmean, np * P->Ns * nk * 16, "chunk means");
+    A((void**)&P->pseg_open, np * P->pseg_V * (1 + kMaxCorr) * nk * 16);
+    A((void**)&P->pcorr, np * kMaxCorr * nk * 8);
+    A((void**)&P->pref, np * nk * 16);
+    A((void**)&P->cmean, np * P->Ns * nk * 16);
   }
-  A((void**)&P->scratch, 64, "scratch");
-  if (d->temperature_K > 0.0) A((void**)&P->qfac, (int64_t)P->n_om * 8, "quantum factor");
-  if (gemm) {
-    A(&P->fmat, (int64_t)2 * P->m_rows * (2 * P->L) * 2, "DFT matrix");
-    A((void**)&P->gscale, np * nk * 4, "operand scales");
-  }
+  if (gemm) A((void**)&P->gscale, np * nk * 4);
   if (d->n_det > 0) {
-    A((void**)&P->masks, (int64_t)d->n_det * nk * 8, "masks");
-    A((void**)&P->pair_slot, (int64_t)P->n_tiles * d->n_det * 4, "detector tile slots");
-    A((void**)&P->Dp, (int64_t)d->n_det * np * P->n_om * 8, "per-probe detector spectra");
+    A((void**)&P->masks, (int64_t)d->n_det * nk * 8);
+    A((void**)&P->pair_slot, (int64_t)P->n_tiles * d->n_det * 4);
+    A((void**)&P->Dp, (int64_t)d->n_det * np * P->n_om * 8);
   }
+  int rc = P->alloc(&P->arena, total, "plan buffers");
   if (rc != TACAW_OK) {
     delete P;
     return rc;
   }
-  auto H2D = [&](void* dst, const void* src, int64_t b) {
-    if (rc == TACAW_OK) rc = hip_check(hipMemcpy(dst, src, (size_t)b, hipMemcpyHostToDevice), "upload");
+  for (const Part& x : parts) *x.p = (char*)P->arena + x.off;
+  P->upload.assign((size_t)table_bytes, 0);  // kept by the plan: the copy is asynchronous
+  auto put = [&](const void* dst, const void* src, int64_t b) {
+    std::memcpy(P->upload.data() + ((const char*)dst - (const char*)P->arena), src, (size_t)b);
   };
-  H2D(P->win_t, wt.data(), P->L * 4);
-  H2D(P->dwin_t, dwt.data(), P->L * 4);
-  H2D(P->tw, twt.data(), P->L * 8);
-  if (P->pseg_tw && rc == TACAW_OK) {
+  put(P->win_t, wt.data(), P->L * 4);
+  put(P->dwin_t, dwt.data(), P->L * 4);
+  put(P->tw, twt.data(), P->L * 8);
+  if (P->pseg_tw) {
     std::vector<double2> pt((size_t)kMaxCorr * P->L, make_double2(0.0, 0.0));
     for (int b = 0; b < P->n_corr; ++b)
       for (int t = 0; t < P->L; ++t) {
-        const double ang = -kTwoPi * (double)(((int64_t)P->bins[b] * t) % P->L) / P->L;
-        pt[(size_t)b * P->L + t] = make_double2(w[t] * std::cos(ang), w[t] * std::sin(ang));
+        const double2 e = tr[((int64_t)P->bins[b] * t) % P->L];
+        pt[(size_t)b * P->L + t] = make_double2(w[t] * e.x, w[t] * e.y);
       }
-    H2D(P->pseg_tw, pt.data(), (int64_t)pt.size() * 16);
+    put(P->pseg_tw, pt.data(), (int64_t)pt.size() * 16);
   }
-  if (P->qfac && rc == TACAW_OK) {
+  if (P->qfac) {
     // E_m = h nu_m, nu_m = m / (L dt) (m < L/2) or (m - L) / (L dt); factor x / (1 - e^-x),
     // x = E_m / (k_B T), limit 1 at E = 0
     const double h_ev_s = 6.62607015e-34 / 1.602176634e-19, kb_ev_k = 8.617333262e-5;
@@ -705,13 +734,20 @@ int tacaw_plan(const tacaw_plan_desc* d, void* hip_stream, tacaw_plan_t* out) {
       const double x = e / (kb_ev_k * d->temperature_K);
       q[r] = x == 0.0 ? 1.0 : x / (-std::expm1(-x));
     }
-    H2D(P->qfac, q.data(), (int64_t)P->n_om * 8);
+    put(P->qfac, q.data(), (int64_t)P->n_om * 8);
   }
-  if (gemm && rc == TACAW_OK) {
+  if (gemm) {
     const std::vector<uint16_t> fm =
-        make_dft_matrix(w, d->transform == TACAW_GEMM_F16X3, P->n_om, P->roi, P->m_rows);
-    H2D(P->fmat, fm.data(), (int64_t)fm.size() * 2);
+        make_dft_matrix(w, tr, d->transform == TACAW_GEMM_F16X3, P->n_om, P->roi, P->m_rows);
+    put(P->fmat, fm.data(), (int64_t)fm.size() * 2);
   }
+  rc = hip_check(hipMemcpyAsync(P->arena, P->upload.data(), (size_t)table_bytes,
+                                hipMemcpyHostToDevice, P->st),
+                 "upload");
+  // what no launch writes reads as zero: the references and sums of plans that keep
+  // none, and the correction bins that a rectangular window does not have
+  if (rc == TACAW_OK)
+    rc = hip_check(launch_fill_zero(P->cref, zero_end - table_bytes, P->st), "plan setup");
   if (d->n_det > 0 && rc == TACAW_OK) {
     rc = hip_check(hipMemcpy(P->masks, d->d_masks, (size_t)d->n_det * nk * 8, hipMemcpyDeviceToDevice),
                    "mask copy");
@@ -720,7 +756,7 @@ int tacaw_plan(const tacaw_plan_desc* d, void* hip_stream, tacaw_plan_t* out) {
       rc = hip_check(hipMemcpy(hm.data(), P->masks, hm.size() * 8, hipMemcpyDeviceToHost), "mask read");
     // one partial slot per (tile, detector) whose mask is non-zero on the tile,
     // numbered detector by detector so each detector's slots are contiguous
-    std::vector<int32_t> slots((size_t)P->n_tiles * d->n_det, -1);
+    P->slots.assign((size_t)P->n_tiles * d->n_det, -1);
     int act = 0;
     for (int dd = 0; dd < d->n_det; ++dd) {
       P->det_slots.off[dd] = act;
@@ -728,32 +764,28 @@ int tacaw_plan(const tacaw_plan_desc* d, void* hip_stream, tacaw_plan_t* out) {
         const int64_t k1 = std::min<int64_t>(nk, (int64_t)(t + 1) * P->W);
         for (int64_t k = (int64_t)t * P->W; k < k1; ++k)
           if (hm[(size_t)dd * nk + k] != 0.0) {
-            slots[(size_t)t * d->n_det + dd] = act++;
+            P->slots[(size_t)t * d->n_det + dd] = act++;
             break;
           }
       }
     }
     P->det_slots.off[d->n_det] = act;
     P->n_pairs = act;
-    H2D(P->pair_slot, slots.data(), (int64_t)slots.size() * 4);
+    if (rc == TACAW_OK)
+      rc = hip_check(hipMemcpyAsync(P->pair_slot, P->slots.data(), P->slots.size() * 4,
+                                    hipMemcpyHostToDevice, P->st),
+                     "upload");
   }
   if (rc == TACAW_OK && (d->flags & TACAW_FLAG_TIME_KERNELS)) {
     for (auto& e : P->ev)
       for (auto& x : e)
         if (rc == TACAW_OK) rc = hip_check(hipEventCreate(&x), "event");
   }
-  if (rc == TACAW_OK) rc = hip_check(hipDeviceSynchronize(), "plan setup");
-  // what no launch writes reads as zero: the references and sums of plans that keep
-  // none, and the correction bins that a rectangular window does not have
-  auto Z = [&](void* p, int64_t b) {
-    if (rc == TACAW_OK && p) rc = hip_check(launch_fill_zero(p, b, P->st), "plan setup");
-  };
-  Z(P->cref, np * nk * 16);
-  Z(P->msum, np * nk * 16);
-  Z(P->xs, np * kMaxCorr * nk * 16);
   if (rc == TACAW_OK) {
     *out = P;
     rc = tacaw_reset(P);
+    // (the caller may go on with another stream)
+    if (rc == TACAW_OK) rc = hip_check(hipStreamSynchronize(P->st), "plan setup");
     if (rc != TACAW_OK) {
       delete P;
       *out = nullptr;
@@ -1473,11 +1505,7 @@ static int backward_impl(tacaw_plan_t P, const void* frames, int32_t probe0, int
   if (global && n_corr == 0)
     TRY(hip_check(launch_bwd_mean_fix(b, P->d.in_dtype, P->st), "adjoint mean term"));
   if (grad_wparam && P->d.window == TACAW_WIN_HANN_WIDTH) {
-    const std::vector<double> w = make_window(P->d.window, P->L, P->d.window_param);
-    const std::vector<double> dw = make_window_dr(P->L, P->d.window_param);
-    double swd = 0.0;
-    for (int t = 0; t < P->L; ++t) swd += w[t] * dw[t];
-    TRY(hip_check(launch_bwd_wparam(b.dwpart, n_tiles, swd / P->sumw2, grad_wparam, P->st),
+    TRY(hip_check(launch_bwd_wparam(b.dwpart, n_tiles, P->sum_wdw / P->sumw2, grad_wparam, P->st),
                   "window-parameter gradient"));
   }
   return TACAW_OK;
