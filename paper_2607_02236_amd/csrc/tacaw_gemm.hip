@@ -22,8 +22,8 @@ typedef __attribute__((__vector_size__(8 * sizeof(_Float16)))) _Float16 f16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 constexpr int kGemmPx = 32;      // pixels per MFMA column block (MFMA N)
-constexpr int kGemmWaves = 4;    // one wave per SIMD
-constexpr int kGemmKC = 256;     // frames per LDS stage (divided by the column blocks)
+constexpr int kGemmWaves = 8;    // two waves per SIMD
+constexpr int kGemmKC = 128;     // frames per LDS stage (divided by the column blocks)
 
 typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
 typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
@@ -64,16 +64,30 @@ __device__ __forceinline__ f32x16 mfma(h8 a, h8 b, f32x16 c) {
 // column 2t + c' (c' = 0 multiplies Re y, 1 multiplies Im y).
 // gscale: [n_probe][n_k] float, the power-of-two scale s of y (fp16; 1 for bf16).
 //
-// Workgroup: 4 waves (one per SIMD), a tile of PX = 32 NB pixels and one row group
+// Workgroup: 8 waves (two per SIMD), a tile of PX = 32 NB pixels and one row group
 // of the GEMM: wave w owns row block blk_lo + w (32 rows) of its group and holds
-// NB accumulator tiles of 32 x 32; as many groups as the rows need at 4 blocks
+// NB accumulator tiles of 32 x 32; as many groups as the rows need at 8 blocks
 // each. Frames are staged through LDS in stages of KC frames, converted to operand
 // order, in two alternating buffers (one barrier per stage).
-// Every load runs a whole stage ahead of its use, so that no wait on a load
-// (vector loads complete in issue order) stalls the MFMAs: during stage st, group u
-// of stage st + 1 is converted into the other buffer at k-step u KSTEPS / G4N and
-// its registers refilled with group u of stage st + 2, and the wave's DFT-matrix
-// fragment of k-step k is refilled with stage st + 1 right after k-step k's MFMAs.
+// Bound by the issue of one wave: in order, a wave alone issues a VALU instruction
+// every 5.5 to 8 cycles on this chip, two waves one every 3 to 5, and an MFMA (32
+// cycles) holds its wave's conversions back. So two waves share a SIMD, and each
+// stage is converted once for 8 row blocks instead of 4 (8 VALU instructions per
+// MFMA before, 3.4 now). What made room in 256 registers: stages of 32 frames, and
+// half of the FP64 accumulators in LDS (they are touched once per chunk).
+// 4 probes x 2048 x 256^2, L = 512, 123 bins, bf16, the whole pass: 4 waves with
+// everything in 496 registers 4.44 ms, now 3.60 ms (MFMA 36 % busy; LDS moves 256 KB
+// per stage, 2048 of its 8400 cycles); one complex128 chunk of 512, all bins: 108 ->
+// 104 us.
+// A column block's products are added in the order of the k-steps, as before, so the
+// sums have the same bits.
+// The DFT-matrix fragments and the frames are loaded a whole stage ahead of their use,
+// so that no wait on a load (vector loads complete in issue order) stalls the MFMAs:
+// during stage st, group u of stage st + 1 is converted into the other buffer at
+// k-step u KSTEPS / G4N and its registers refilled with group u of stage st + 2, and
+// the wave's DFT-matrix fragment of k-step k is refilled with stage st + 1 right
+// after k-step k's MFMAs. The next k-step's B fragments are read as soon as the last
+// product that uses the register set is issued.
 // SRC: 0 every frame from the push buffer; 1 frames before push_begin from the
 // per-frame ring (immediate and deferred streaming); 2 every frame from the ring
 // stored per tile of PX pixels ([slot][tile][row][PX]).
@@ -101,9 +115,13 @@ __global__ void __launch_bounds__(64 * kGemmWaves)
   static_assert(L % KC == 0 && (KC / 4) % SG == 0 && G4N >= 1 && G4N <= KSTEPS, "staging");
 
   // B operand stages: [2][nb][hi, lo][kstep][lane][8], 16-bit; reused at the end of a
-  // probe for the FP64 reductions
-  constexpr int RED = 16 * kGemmWaves * PX * 4;  // 16-bit slots of the partials' rows
+  // probe for the FP64 reductions (8 rows of each wave's block)
+  constexpr int PXP = PX + 4;  // doubles per row of the FP64 arrays (bank spread, see the partials)
+  constexpr int RED = 8 * kGemmWaves * PXP * 4;
   __shared__ __attribute__((aligned(16))) unsigned short bst[2 * BUF > RED ? 2 * BUF : RED];
+  // FP64 accumulators of rows 8..15 of each wave's 16 output rows (rows 0..7 stay in
+  // registers): [wave][row - 8][PXP]
+  __shared__ double lacc[kGemmWaves * 8 * PXP];
   __shared__ double s_mask[DP ? kMaxDet * PX : 1];
   __shared__ double2 s_ref[TRACK ? PX : 1];
   __shared__ double2 s_xs[TRACK ? kMaxCorr * PX : 1];
@@ -162,8 +180,8 @@ __global__ void __launch_bounds__(64 * kGemmWaves)
   const int64_t ksc = ks < n_k ? ks : (int64_t)n_k - 1;
   const int64_t poff = pix_off(ksc, a.nx, a.row_stride);
   const int H = a.hop;
-  // this lane's DFT-matrix row; a wave without a block reads a valid one and its
-  // results are dropped (its SIMD has no other wave, so this costs no MFMA time)
+  // this lane's DFT-matrix row; a wave without a block reads a valid one and only
+  // stages
   const int64_t arow = 32 * (int64_t)min(blk, n_blocks - 1) + col;
 
   // frame f (absolute) of probe i at pixel k
@@ -186,11 +204,20 @@ __global__ void __launch_bounds__(64 * kGemmWaves)
     }
   };
 
-  double acc64[NB][8];
+  // FP64 accumulator q of column block nb: output row 4 (q / 2) + 2 half + q % 2 of the
+  // wave's block; q < 4 in registers, the others in LDS
+  double acc64[NB][4];
+  double* const la = lacc + (wave * 8 + 2 * half) * PXP + col;
+  auto lslot64 = [&](int nb, int q) -> double& {
+    return la[(4 * (q / 2 - 2) + q % 2) * PXP + kGemmPx * nb];
+  };
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-    for (int q = 0; q < 8; ++q) acc64[nb][q] = 0.0;
+    for (int q = 0; q < 8; ++q) {
+      if (q < 4) acc64[nb][q] = 0.0;
+      else lslot64(nb, q) = 0.0;
+    }
 
   for (int i = 0; i < a.n_probes; ++i) {
     const int p = a.probe0 + i;
@@ -369,36 +396,13 @@ __global__ void __launch_bounds__(64 * kGemmWaves)
       for (int u = 0; u < G4N; ++u) load_group(min(1, n_stages - 1), u);
       __syncthreads();
     }
-    // The k-step sequence has no branches (which would make the compiler's waits on
-    // loads conservative): the last stages reload the last stage's frames and DFT
-    // fragments (valid addresses) and convert them into the idle buffer uncounted.
+    // The last stages reload the last stage's frames and DFT fragments (valid
+    // addresses) and convert them into the idle buffer uncounted: no branches.
     for (int st = 0; st < n_stages; ++st) {
       const unsigned short* bb = bst + (st & 1) * BUF;
       const bool next = st + 1 < n_stages;
       const int st1 = min(st + 1, n_stages - 1), st2 = min(st + 2, n_stages - 1);
-      // B fragments from LDS, one k-step ahead within the stage
-      h8 bh[2][NB], bl[2][NB];
-      auto b_load = [&](int k) {
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-          bh[k & 1][nb] = *reinterpret_cast<const h8*>(&bb[(((nb * 2 + 0) * KSTEPS + k) * 64 + lane) * 8]);
-          bl[k & 1][nb] = *reinterpret_cast<const h8*>(&bb[(((nb * 2 + 1) * KSTEPS + k) * 64 + lane) * 8]);
-        }
-      };
-      b_load(0);
-#pragma unroll
-      for (int kst = 0; kst < KSTEPS; ++kst) {
-        if (kst + 1 < KSTEPS) b_load(kst + 1);
-        const int c = kst & 1;
-        // each product over the column blocks in turn: an MFMA's accumulator comes
-        // from the one NB MFMAs earlier, past its latency
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[nb] = mfma<PREC>(ah[kst], bh[c][nb], acc[nb]);
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[nb] = mfma<PREC>(ah[kst], bl[c][nb], acc[nb]);
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[nb] = mfma<PREC>(al[kst], bh[c][nb], acc[nb]);
-        a_load(st1, kst);
+      auto stage_group = [&](int kst) {
 #pragma unroll
         for (int u = 0; u < G4N; ++u) {
           if (u * KSTEPS / G4N == kst) {
@@ -406,19 +410,38 @@ __global__ void __launch_bounds__(64 * kGemmWaves)
             load_group(st2, u);
           }
         }
-      }
-      // one wave per SIMD issues in order: interleave the conversion (VALU) with the
-      // MFMAs, so that it runs while the matrix core works, and issue the next
-      // k-step's B fragments (2 NB LDS reads) before this k-step's 3 NB MFMAs, which
-      // then hide their latency (each read placed just before its MFMA waited for it)
+      };
+      if (!active) {  // a wave without rows only stages
 #pragma unroll
-      for (int kst = 0; kst < KSTEPS; ++kst) {
-        if (kst == 0) __builtin_amdgcn_sched_group_barrier(0x100, (KSTEPS > 1 ? 4 : 2) * NB, 0);
-        else if (kst + 1 < KSTEPS) __builtin_amdgcn_sched_group_barrier(0x100, 2 * NB, 0);
+        for (int kst = 0; kst < KSTEPS; ++kst) stage_group(kst);
+      } else {
+        h8 bh[NB], bl[NB];
+        auto bh_load = [&](int k) {
 #pragma unroll
-        for (int i = 0; i < 3 * NB; ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-          __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);  // VALU
+          for (int nb = 0; nb < NB; ++nb)
+            bh[nb] = *reinterpret_cast<const h8*>(&bb[(((nb * 2 + 0) * KSTEPS + k) * 64 + lane) * 8]);
+        };
+        auto bl_load = [&](int k) {
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb)
+            bl[nb] = *reinterpret_cast<const h8*>(&bb[(((nb * 2 + 1) * KSTEPS + k) * 64 + lane) * 8]);
+        };
+        bh_load(0);
+        bl_load(0);
+#pragma unroll
+        for (int kst = 0; kst < KSTEPS; ++kst) {
+          // each product over the column blocks in turn: an MFMA's accumulator comes
+          // from the one NB MFMAs earlier, past its latency
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) acc[nb] = mfma<PREC>(ah[kst], bh[nb], acc[nb]);
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) acc[nb] = mfma<PREC>(ah[kst], bl[nb], acc[nb]);
+          if (kst + 1 < KSTEPS) bl_load(kst + 1);
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) acc[nb] = mfma<PREC>(al[kst], bh[nb], acc[nb]);
+          if (kst + 1 < KSTEPS) bh_load(kst + 1);
+          a_load(st1, kst);
+          stage_group(kst);
         }
       }
       if (st % SPC == SPC - 1 && active) {
@@ -444,13 +467,16 @@ __global__ void __launch_bounds__(64 * kGemmWaves)
                 }
               }
             }
+            double add = 0.0;
             if (corr) {
               // the per-chunk mean kernel supplies these rows' whole FP64 value
-              if (!a.corr_skip) acc64[nb][q] += (double)xr * (double)xr + (double)xi * (double)xi;
+              if (!a.corr_skip) add = (double)xr * (double)xr + (double)xi * (double)xi;
             } else {
               const float pw = xr * xr + xi * xi;
-              acc64[nb][q] += (double)(pw * inv2[nb]);
+              add = (double)(pw * inv2[nb]);
             }
+            if (q < 4) acc64[nb][q] += add;
+            else lslot64(nb, q) += add;
           }
 #pragma unroll
           for (int v = 0; v < 16; ++v) acc[nb][v] = 0.0f;
@@ -491,29 +517,39 @@ __global__ void __launch_bounds__(64 * kGemmWaves)
     }
 
     if constexpr (DP) {
-      // cumulative detector partials of this group's output rows
+      // cumulative detector partials of this group's output rows: rows 0..7 of each
+      // block staged from registers, rows 8..15 are in LDS already
       __syncthreads();
-      double* sd = reinterpret_cast<double*>(bst);  // [group rows][PX]
+      double* sd = reinterpret_cast<double*>(bst);  // [wave][row][PXP]
       const int r_lo = 16 * blk_lo, r_hi = min(n_om, 16 * blk_hi);
+      if (active) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int r = 16 * blk + 4 * (q / 2) + 2 * half + (q % 2);
-        if (active && r < r_hi) {
+        for (int q = 0; q < 4; ++q) {
+          const int r = 8 * wave + 4 * (q / 2) + 2 * half + (q % 2);
 #pragma unroll
-          for (int nb = 0; nb < NB; ++nb) sd[(r - r_lo) * PX + kGemmPx * nb + col] = acc64[nb][q];
+          for (int nb = 0; nb < NB; ++nb) sd[r * PXP + kGemmPx * nb + col] = acc64[nb][q];
         }
       }
       __syncthreads();
       const int32_t* slots = a.pair_slot + (int64_t)tile * a.n_det;
-      for (int rr = tid; rr < r_hi - r_lo; rr += NT) {
+      // four threads per row (all 512 for the 128 rows of a full group), pixels dealt
+      // in turn: 8 rows x 4 threads read 32 distinct bank pairs
+      const int part = tid & 3;
+      for (int r4 = tid >> 2; r4 < 16 * kGemmWaves; r4 += NT / 4) {
+        const int rr = min(r4, r_hi - r_lo - 1);  // (whole waves: the shuffles need every lane)
+        const int b8 = 8 * (rr / 16) + rr % 8;    // block rr / 16, row rr % 16
+        const double* row = (rr % 16 < 8 ? sd : lacc) + b8 * PXP + part;
         for (int d = 0; d < a.n_det; ++d) {
           const int slot = slots[d];  // -1: this detector's mask is zero on the tile
           if (slot < 0) continue;
           double dsum = 0.0;
-#pragma unroll
-          for (int x = 0; x < PX; ++x) dsum += s_mask[d * PX + x] * sd[rr * PX + x];
+#pragma unroll 8
+          for (int x = 0; x < PX; x += 4) dsum += s_mask[d * PX + x + part] * row[x];
+          dsum += __shfl_xor(dsum, 1, 64);
+          dsum += __shfl_xor(dsum, 2, 64);
           // cumulative over probes 0..i
-          a.dpart[((int64_t)slot * a.n_probes + i) * n_om + r_lo + rr] = dsum;
+          if (part == 0 && r4 == rr)
+            a.dpart[((int64_t)slot * a.n_probes + i) * n_om + r_lo + rr] = dsum;
         }
       }
     }
@@ -527,7 +563,8 @@ __global__ void __launch_bounds__(64 * kGemmWaves)
       for (int nb = 0; nb < NB; ++nb) {
         if (cvalid[nb]) {
           double* sp_ = a.S + (int64_t)r * n_k + kcol[nb];
-          *sp_ = a.s_store ? acc64[nb][q] : *sp_ + acc64[nb][q];
+          const double av = q < 4 ? acc64[nb][q < 4 ? q : 0] : lslot64(nb, q);
+          *sp_ = a.s_store ? av : *sp_ + av;
         }
       }
     }
@@ -535,7 +572,7 @@ __global__ void __launch_bounds__(64 * kGemmWaves)
 }
 
 // 4 column blocks (128 pixels) per workgroup, so each DFT-matrix fragment feeds 12
-// MFMAs; rows beyond 4 waves x 32 go to more row groups, each staging the same
+// MFMAs; rows beyond 8 waves x 32 go to more row groups, each staging the same
 // frames (from L2 after the first)
 constexpr int kGemmNB = 4;
 static int gemm_groups(int n_om) {
