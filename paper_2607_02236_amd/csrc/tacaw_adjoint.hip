@@ -85,7 +85,14 @@ __device__ __forceinline__ float2 rot_g(float2 x, int e) {
 // pass): the frames of chunk s get 2 w g_s - M_s / L with
 // M_s = 2 sum_b G(b) conj(W(b)) X_s(b) over the bins where W != 0, posted by the
 // bin-role threads that hold those bins.
-template <int L, typename InT, bool DW, int MT>
+// HALF_HOP: hop = L/2 (else hop = L): the second half of a chunk's raw samples is the
+// next chunk's first half, so each frame is read once, and the first half of its
+// gradient is carried until the next chunk adds to it. With hop = L neither takes
+// registers, so that at L = 512 with DW the kernel fits its 256 (88 bytes of scratch
+// before). Bound by latency at two waves per SIMD, then by HBM: 16 probes x 1024
+// frames of 128^2, L = H = 512, 4.3 GB read and written: 1390 -> 1105 us. (The
+// forward's sums of the next probe loaded a chunk ahead through LDS: no change.)
+template <int L, typename InT, bool DW, int MT, bool HALF_HOP>
 __global__ void __launch_bounds__(BwdShape<L>::W*(L / BwdShape<L>::N1))
     bwd_kernel(const BwdArgs a) {
   constexpr int N1 = BwdShape<L>::N1;
@@ -160,8 +167,7 @@ __global__ void __launch_bounds__(BwdShape<L>::W*(L / BwdShape<L>::N1))
     return g;
   };
 
-  const int H = a.hop;
-  const bool half_hop = (2 * H == L);
+  constexpr int H = HALF_HOP ? L / 2 : L;
   double dA = 0.0, dLval = 0.0;
   float Gt[N1];  // weights of the thread's bins (they change per probe only through gDp)
 
@@ -179,22 +185,36 @@ __global__ void __launch_bounds__(BwdShape<L>::W*(L / BwdShape<L>::N1))
     asm volatile("" : "+s"(gstride));
     return (char*)base + (int64_t)ii * a.pstride * ESZ + (int64_t)ss * H * row_bytes + n1 * gstride;
   };
+  // this workgroup's probes of the call: [i_lo, i_hi)
+  const int i_lo = blockIdx.y * a.split_probes, i_hi = min(a.n_probes, i_lo + a.split_probes);
   // raw samples of the next chunk, loaded one chunk ahead
   InT pre[N1];
 #pragma unroll
-  for (int n1 = 0; n1 < N1; ++n1) pre[n1] = buffer_load<InT>(group(a.in, 0, 0, n1), group_bytes, lane_off);
+  for (int n1 = 0; n1 < N1; ++n1) pre[n1] = buffer_load<InT>(group(a.in, i_lo, 0, n1), group_bytes, lane_off);
 
-  for (int i = 0; i < a.n_probes; ++i) {
+  float gcorr[kMaxCorr];  // MT 2: the FP32 weights of the correction bins
+  for (int i = i_lo; i < i_hi; ++i) {
     const int p = a.probe0 + i;
-    if (i == 0 || a.gDp) {
+    if (i == i_lo || a.gDp) {
 #pragma unroll
       for (int t = 0; t < N1; ++t) Gt[t] = (float)weight(bin(t), p);
+      if constexpr (MT == 2) {
+#pragma unroll
+        for (int b = 0; b < kMaxCorr; ++b)
+          gcorr[b] = b < a.n_corr ? (float)weight(b == 0 ? 0 : (b == 1 ? 1 : L - 1), p) : 0.0f;
+      }
     }
     // mu = c + delta, delta = (sum over the used frames of psi - c) / N_used
     double2 mu = make_double2(0.0, 0.0), delta = make_double2(0.0, 0.0);
+    double2 xs[MT == 2 ? kMaxCorr : 1];
     if constexpr (MT == 1 || MT == 2) {
       const double2 cr = a.cref[(int64_t)p * n_k + kc];
       const double2 ms = a.msum[(int64_t)p * n_k + kc];
+      if constexpr (MT == 2) {  // (all loads together)
+#pragma unroll
+        for (int b = 0; b < kMaxCorr; ++b)
+          if (b < a.n_corr) xs[b] = a.xs[((int64_t)p * kMaxCorr + b) * n_k + kc];
+      }
       delta = make_double2(ms.x * a.inv_nused, ms.y * a.inv_nused);
       mu = make_double2(cr.x + delta.x, cr.y + delta.y);
     }
@@ -203,11 +223,12 @@ __global__ void __launch_bounds__(BwdShape<L>::W*(L / BwdShape<L>::N1))
     double2 fixd = make_double2(0.0, 0.0);
     if constexpr (MT == 2) {
       double2 gm = make_double2(0.0, 0.0);
-      for (int b = 0; b < a.n_corr; ++b) {
-        const int m = b == 0 ? 0 : (b == 1 ? 1 : L - 1);
-        const double g = 2.0 * (double)(float)weight(m, p);  // the FP32 weight the transform uses
+#pragma unroll
+      for (int b = 0; b < kMaxCorr; ++b) {
+        if (b >= a.n_corr) continue;
+        const double g = 2.0 * (double)gcorr[b];  // the FP32 weight the transform uses
         const double2 wb = a.wbin[b];
-        const double2 x = a.xs[((int64_t)p * kMaxCorr + b) * n_k + kc];
+        const double2 x = xs[b];
         // sum_s X_s(m) = sum_s X'_s(m) - N_s delta W(m)
         const double sx = x.x - a.n_seg * (delta.x * wb.x - delta.y * wb.y);
         const double sy = x.y - a.n_seg * (delta.x * wb.y + delta.y * wb.x);
@@ -217,9 +238,11 @@ __global__ void __launch_bounds__(BwdShape<L>::W*(L / BwdShape<L>::N1))
       fixd = make_double2(gm.x * a.inv_nused, gm.y * a.inv_nused);
       fix = make_float2((float)fixd.x, (float)fixd.y);
     }
-    float2 carry[HALF];
+    float2 carry[HALF_HOP ? HALF : 1];
+    if constexpr (HALF_HOP) {
 #pragma unroll
-    for (int u = 0; u < HALF; ++u) carry[u] = make_float2(0.f, 0.f);
+      for (int u = 0; u < HALF; ++u) carry[u] = make_float2(0.f, 0.f);
+    }
     double2 gsum = make_double2(0.0, 0.0);
 
     for (int s = 0; s < a.n_seg; ++s) {
@@ -243,12 +266,17 @@ __global__ void __launch_bounds__(BwdShape<L>::W*(L / BwdShape<L>::N1))
       // prefetch the next chunk (or the next probe's first chunk)
       {
         const bool next_chunk = s + 1 < a.n_seg;
-        if (next_chunk || i + 1 < a.n_probes) {
+        if (next_chunk || i + 1 < i_hi) {
           const int ii = next_chunk ? i : i + 1;
           const int ss = next_chunk ? s + 1 : 0;
+          if constexpr (HALF_HOP) {
+#pragma unroll
+            for (int n1 = 0; n1 < HALF; ++n1) pre[n1] = pre[n1 + HALF];
+          }
 #pragma unroll
           for (int n1 = 0; n1 < N1; ++n1)
-            pre[n1] = buffer_load<InT>(group(a.in, ii, ss, n1), group_bytes, lane_off);
+            if (!HALF_HOP || n1 >= HALF || !next_chunk)
+              pre[n1] = buffer_load<InT>(group(a.in, ii, ss, n1), group_bytes, lane_off);
         }
       }
       // ---- forward transform: time layout -> bin layout X[t] = X(bin(t)); the
@@ -385,7 +413,7 @@ __global__ void __launch_bounds__(BwdShape<L>::W*(L / BwdShape<L>::N1))
       for (int n1 = 0; n1 < N1; ++n1) {
         float2 o = v[n1];
         bool store = true;
-        if (half_hop) {
+        if constexpr (HALF_HOP) {
           if (n1 < HALF) {
             o.x += carry[n1].x;
             o.y += carry[n1].y;
@@ -448,8 +476,9 @@ __global__ void __launch_bounds__(BwdShape<L>::W*(L / BwdShape<L>::N1))
     __syncthreads();
   }
   if (tid == 0) {
-    a.dwpart[2 * tile] = red[0];
-    a.dwpart[2 * tile + 1] = red[NT];
+    const int64_t e = (int64_t)blockIdx.y * gridDim.x + tile;
+    a.dwpart[2 * e] = red[0];
+    a.dwpart[2 * e + 1] = red[NT];
   }
 }
 
@@ -495,10 +524,17 @@ template <int L>
 static hipError_t launch_bl(int in_dtype, const BwdArgs& a, int n_tiles, hipStream_t st) {
   constexpr int NT = BwdShape<L>::W * (L / BwdShape<L>::N1);
   const bool dw = a.dwin_t != nullptr;
+  const int splits = (a.n_probes + a.split_probes - 1) / a.split_probes;
   const int mt = a.per_chunk ? 3 : (a.mean_global ? (a.n_corr > 0 ? 2 : 1) : 0);
   auto go = [&](auto in_t, auto dw_c, auto mt_c) {
-    hipLaunchKernelGGL((bwd_kernel<L, decltype(in_t), decltype(dw_c)::value, decltype(mt_c)::value>),
-                       dim3(n_tiles), dim3(NT), 0, st, a);
+    if (a.hop == L)
+      hipLaunchKernelGGL(
+          (bwd_kernel<L, decltype(in_t), decltype(dw_c)::value, decltype(mt_c)::value, false>),
+          dim3(n_tiles, splits), dim3(NT), 0, st, a);
+    else
+      hipLaunchKernelGGL(
+          (bwd_kernel<L, decltype(in_t), decltype(dw_c)::value, decltype(mt_c)::value, true>),
+          dim3(n_tiles, splits), dim3(NT), 0, st, a);
   };
   using T0 = std::false_type;
   using T1 = std::true_type;

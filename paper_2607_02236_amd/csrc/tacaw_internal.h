@@ -185,6 +185,7 @@ struct BwdArgs {
   int32_t nx;
   void* grad;              // same layout as in
   int32_t n_k, probe0, n_probes, n_probe_total, n_seg, hop, n_det;
+  int32_t split_probes;    // probes per workgroup (the grid is tiles x splits of the probes)
   int32_t n_om, roi_half;  // output rows and energy window (bin m -> row (m + M) mod L)
   int32_t mean_global;
   int32_t per_chunk;       // per-chunk mean: chunk s subtracts cmean[p][s][k]
@@ -206,7 +207,7 @@ struct BwdArgs {
   double kappa_S, kappa_p; // normalisations of S and S_p
   const double* qfac;      // [n_om] quantum-statistics factor per row, or null
   double2* gmean;          // [n_probes][n_k] sum over chunks and t of w * grad_y (mean term)
-  double* dwpart;          // [n_tiles][2] partial sums: r-derivative term, loss value
+  double* dwpart;          // [splits][n_tiles][2] partial sums: r-derivative term, loss value
 };
 hipError_t launch_bwd(int L, int in_dtype, const BwdArgs& a, int n_tiles, hipStream_t st);
 int bwd_tile_pixels(int L);
