@@ -860,7 +860,7 @@ hipError_t launch_detector_prep(double* D, int64_t n_d, const double* src, doubl
 
 // D[d][m] += sum over a pixel chunk of M_d(k) S(m, k): each block takes kDetBins
 // bins and a chunk of pixels (coalesced rows of S), reduces across each wave
-// with lane shuffles and adds one value per (wave, bin, detector) atomically.
+// with lane shuffles and adds one value per (block, bin, detector) atomically.
 constexpr int kDetBins = 4;
 template <int ND>
 __global__ void detector_kernel(const double* S, const double* masks, int32_t L, int32_t n_k,
@@ -868,6 +868,7 @@ __global__ void detector_kernel(const double* S, const double* masks, int32_t L,
   const int m0 = blockIdx.y * kDetBins;
   const int64_t k0 = (int64_t)blockIdx.x * chunk;
   const int64_t k1 = (k0 + chunk < n_k) ? k0 + chunk : n_k;
+  __shared__ double red[4][kDetBins * ND];  // blocks of 4 waves
   double acc[kDetBins][ND], f[kDetBins];
 #pragma unroll
   for (int b = 0; b < kDetBins; ++b) {
@@ -893,19 +894,24 @@ __global__ void detector_kernel(const double* S, const double* masks, int32_t L,
       double v = acc[b][d];
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-      if ((threadIdx.x & 63) == 0 && m0 + b < L) atomicAdd(&D[(int64_t)d * L + m0 + b], v);
+      if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][b * ND + d] = v;
     }
   }
+  __syncthreads();
+  const int e = threadIdx.x, b = e / ND, d = e % ND;
+  if (e < kDetBins * ND && m0 + b < L)
+    atomicAdd(&D[(int64_t)d * L + m0 + b], (red[0][e] + red[1][e]) + (red[2][e] + red[3][e]));
 }
 
 template <int ND>
 static void launch_det_nd(const double* S, const double* masks, int32_t L, int32_t n_k,
                           double kappa, const double* q, double* D, hipStream_t st) {
-  // 16384 pixels per block, fewer while the grid is below 8 blocks per CU: the
-  // 16 blocks of 64^2 pixels and 64 bins walked 16 pixels per thread one after another
+  // 16384 pixels per block, fewer while the grid is below 8 blocks per CU, but at most
+  // 32 blocks add to one value (256^2 pixels, 123 bins, 4 masks: 47 us with 16384 pixels per
+  // block, 29 us with 2048, 181 us with 512 and one atomic per wave, which queue up)
   const int64_t rows = (L + kDetBins - 1) / kDetBins;
   int chunk = 16384;
-  while (chunk > 512 && (n_k + chunk - 1) / chunk * rows < 2048) chunk /= 2;
+  while (chunk > 512 && (n_k + chunk - 1) / chunk * rows < 2048 && n_k <= 32 * (chunk / 2)) chunk /= 2;
   dim3 g((n_k + chunk - 1) / chunk, (unsigned)rows);
   hipLaunchKernelGGL((detector_kernel<ND>), g, dim3(256), 0, st, S, masks, L, n_k, chunk, kappa, q, D);
 }
