@@ -436,6 +436,20 @@ __global__ void __launch_bounds__(FftShape<L>::W*(L / FftShape<L>::N1))
         } else {
           take_pre(0, C3{});
         }
+        if constexpr (MIX && !FULL) {
+          // The last chunk's second half is the next push's first half: its raw samples
+          // go to the ring from here. The launch holds at least two chunks, so the
+          // ring rows this may overwrite were read before the first one's barrier.
+          if (a.keep && s + 1 == a.s_hi && kvalid) {
+            const int64_t slot = p % a.n_slots;
+#pragma unroll
+            for (int n1 = HALF; n1 < N1; ++n1) {
+              const int64_t f0 = seg0 + N2 * n1;
+              char* rb = (char*)a.ring + (slot * a.ring_depth + f0 % a.ring_depth) * n_k * ESZ;
+              buffer_store<InT>(pre[n1], rb, ring_bytes, ring_off);
+            }
+          }
+        }
         // prefetch the next chunk's new samples (or the next probe's first chunk)
         const bool next_chunk = s + 1 < a.s_hi;
         if (next_chunk || i + 1 < a.n_probes) {

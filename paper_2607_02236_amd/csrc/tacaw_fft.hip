@@ -19,7 +19,6 @@ static void launch_lean(const SegArgs& a, int n_tiles, hipStream_t st) {
 template <int L, typename InT, bool SUB64>
 static hipError_t launch_t(const SegArgs& a, int n_tiles, hipStream_t st) {
   constexpr int NT = FftShape<L>::W * (L / FftShape<L>::N1);
-  constexpr int N2 = L / FftShape<L>::N1;
   const bool lean = (2 * a.hop == L || a.hop == L) && !a.from_ring;
   // frames before the push, in the first chunk only (see MIX)
   const bool mix = lean && (int64_t)a.s_lo * a.hop < a.push_begin;
@@ -27,10 +26,8 @@ static hipError_t launch_t(const SegArgs& a, int n_tiles, hipStream_t st) {
   const int64_t span = pix_off((int64_t)a.n_k - 1, a.nx, a.row_stride) + 1;
   const bool narrow =
       ((int64_t)(L - 1) * a.fstride + span) * (int64_t)sizeof(InT) < ((int64_t)1 << 31);
-  // the ring's row groups are addressed with 31-bit offsets; the float2 form with
-  // FP64 differences (exact mean) takes each series in one push
+  // the float2 form with FP64 differences (exact mean) takes each series in one push
   constexpr bool kMixed = !(SUB64 && sizeof(InT) == 8);
-  const bool ring_fits = (int64_t)N2 * a.n_k * (int64_t)sizeof(InT) < ((int64_t)1 << 31);
   if (lean && !mix) {
     if (a.hop == L) {
       if (narrow) launch_lean<L, InT, SUB64, 3, true, false>(a, n_tiles, st);
@@ -42,7 +39,7 @@ static hipError_t launch_t(const SegArgs& a, int n_tiles, hipStream_t st) {
     return hipGetLastError();
   }
   if constexpr (kMixed) {
-    if (mix && ring_fits) {
+    if (mix && ring_group_fits(L / FftShape<L>::N1, a.n_k, sizeof(InT))) {
       if (a.hop == L) {
         if (narrow) launch_lean<L, InT, SUB64, 3, true, true>(a, n_tiles, st);
         else launch_lean<L, InT, SUB64, 1, true, true>(a, n_tiles, st);
@@ -80,6 +77,14 @@ void seg_fft_split(int L, int* n1, int* n2) {
   }
   *n1 = a;
   *n2 = a ? L / a : 0;
+}
+
+bool seg_fft_keeps(int L, int in_dtype, bool sub64, const SegArgs& a) {
+  int n1, n2;
+  seg_fft_split(L, &n1, &n2);
+  return 2 * a.hop == L && !a.from_ring && (int64_t)a.s_lo * a.hop < a.push_begin &&
+         a.s_hi - a.s_lo >= 2 && !(sub64 && in_dtype == 0) &&
+         ring_group_fits(n2, a.n_k, in_dtype == 1 ? 16 : 8);
 }
 
 bool seg_fft_supported(int L) {

@@ -34,6 +34,8 @@ struct SegArgs {
                            // frame f at row f mod D
   int64_t ring_depth;      // D (>= L, < 2^30)
   int32_t ring_row_lo;     // (s_lo * hop) mod D: ring row of the launch's first chunk
+  int32_t keep;            // the chunk kernel stores the last chunk's second half in the ring
+                           // (see seg_fft_keeps)
   int32_t from_ring;       // whole-series variant: every chunk is read from the ring
   int32_t ring_tiles;      // > 0: the ring is stored per pixel tile, [n_slots][ring_tiles][D][W]
                            // (W = the chunk kernel's tile width); 0: [n_slots][D][n_k]
@@ -73,6 +75,14 @@ hipError_t launch_seg_fft(int L, int in_dtype, bool sub64, const SegArgs& a, int
 // the whole-series variant reading every frame from the ring (a.from_ring, 2 hop = L)
 hipError_t launch_seg_fft_ring(int L, int in_dtype, bool sub64, const SegArgs& a, int n_tiles,
                                hipStream_t st);
+// A row group (n2 contiguous frames) of the per-frame ring is within 31-bit offsets
+inline bool ring_group_fits(int n2, int32_t n_k, int esz) {
+  return (int64_t)n2 * n_k * esz < ((int64_t)1 << 31);
+}
+// Whether the launch of these chunks can store the frames [s_hi hop, s_hi hop + hop), the
+// last chunk's second half, in the ring itself (a.keep): the ring-and-push variant,
+// hop = L/2, with at least two chunks
+bool seg_fft_keeps(int L, int in_dtype, bool sub64, const SegArgs& a);
 int seg_fft_tile_pixels(int L);
 void seg_fft_split(int L, int* n1, int* n2);  // L = N1 * N2 of the push kernel's tables
 bool seg_fft_supported(int L);

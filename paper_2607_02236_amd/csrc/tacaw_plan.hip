@@ -303,10 +303,11 @@ static RefSamples first_frame_sample() {
 // One chunk-kernel launch over chunks [s_lo, s_hi) of probes [probe0, probe0 + n_probes),
 // followed by the per-probe detector partial reduce. from_ring: every frame is read from
 // the ring (deferred mode); otherwise from the push buffer `src` (frame push_begin at its
-// row 0) and, for frames before push_begin, from the ring.
+// row 0) and, for frames before push_begin, from the ring. keep (in: the frames from
+// s_hi * hop on are wanted in the ring; out: the launch stores the first hop of them).
 static int run_chunks(tacaw_plan_t P, const void* src, int64_t pstride, int64_t fstride,
                       int64_t push_begin, bool from_ring, int probe0, int n_probes, int s_lo,
-                      int s_hi) {
+                      int s_hi, bool* keep = nullptr) {
   SegArgs g{};
   g.in = src;
   g.pstride = pstride;
@@ -346,6 +347,11 @@ static int run_chunks(tacaw_plan_t P, const void* src, int64_t pstride, int64_t 
   g.dpart = P->dpart;
   g.gscale = P->gscale;
   const bool sub64 = P->d.in_dtype == TACAW_C128 || P->strategy == kRefExactMean;
+  if (keep) {
+    *keep = *keep && !transform_is_gemm(P->d.transform) &&
+            seg_fft_keeps(P->L, P->d.in_dtype, sub64, g);
+    g.keep = *keep ? 1 : 0;
+  }
   const bool timed = P->n_timed < kMaxTimed && P->ev[0][0];
   if (timed) TRY(hip_check(hipEventRecord(P->ev[P->n_timed][0], P->st), "event"));
   if (transform_is_gemm(P->d.transform))
@@ -1178,12 +1184,16 @@ int tacaw_push_frames(tacaw_plan_t P, const void* frames, int32_t probe0, int32_
   P->n_timed = 0;
   if (!P->deferred) {
     // 2. every chunk completed by this push, read from the push (and the ring)
-    if (s_hi > s_lo) TRY(run_chunks(P, frames, pstride, fstride, a, false, probe0, n_probes, s_lo, s_hi));
-    // 3. keep what later chunks need
+    bool kept = need_ring_write;
+    if (s_hi > s_lo)
+      TRY(run_chunks(P, frames, pstride, fstride, a, false, probe0, n_probes, s_lo, s_hi, &kept));
+    else
+      kept = false;
+    // 3. keep what later chunks need (the chunk launch may have stored the first hop of it)
     if (need_ring_write)
       TRY(hip_check(launch_ring_store(frames, P->d.in_dtype, pstride, fstride, P->d.nx, P->rs, a,
-                                      keep_lo, keep_hi, probe0, n_probes, P->n_slots, P->D,
-                                      P->n_k, 0, P->ring, P->st),
+                                      kept ? (int64_t)s_hi * P->H + P->H : keep_lo, keep_hi, probe0,
+                                      n_probes, P->n_slots, P->D, P->n_k, 0, P->ring, P->st),
                     "ring store"));
   } else {
     // deferred: the push is copied into the ring; completed chunks run from there
