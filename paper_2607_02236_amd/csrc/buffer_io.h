@@ -9,29 +9,32 @@
 namespace tacaw {
 
 // Raw buffer load of one element at base + off (off < range, else 0): the base
-// and the range live in scalar registers, the offset in one VGPR.
-template <typename T>
+// and the range live in scalar registers, the offset in one VGPR. NT: non-temporal,
+// for data that this launch reads once.
+template <typename T, bool NT = false>
 __device__ __forceinline__ T buffer_load(const char* base, uint32_t range, uint32_t off) {
+  constexpr int aux = NT ? 2 : 0;  // the NT bit of a CDNA3/4 buffer access
   __amdgpu_buffer_rsrc_t r =
       __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)range, 0x00020000);
   if constexpr (sizeof(T) == 8) {
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, aux));
   } else {
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0));
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, aux));
   }
 }
 
 // The same with a scalar offset: element at base + soffset + off, range counted
 // from base (one descriptor serves several row groups).
-template <typename T>
+template <typename T, bool NT = false>
 __device__ __forceinline__ T buffer_load_so(const char* base, uint32_t range, uint32_t off,
                                             uint32_t soff) {
+  constexpr int aux = NT ? 2 : 0;  // the NT bit of a CDNA3/4 buffer access
   __amdgpu_buffer_rsrc_t r =
       __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)range, 0x00020000);
   if constexpr (sizeof(T) == 8) {
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, (int)soff, 0));
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, (int)soff, aux));
   } else {
-    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, (int)soff, 0));
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, (int)soff, aux));
   }
 }
 

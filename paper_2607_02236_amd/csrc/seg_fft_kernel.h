@@ -88,6 +88,10 @@ struct FftShape<200> {
 // variant reading every frame from the ring (deferred streaming); MODE 3: MODE 1
 // when a whole chunk of frames spans less than 2 GiB, so one buffer descriptor per
 // chunk serves all row groups through a scalar offset (fewer scalar registers).
+// MODE 5: MODE 3 with non-temporal loads, for large inputs in whole cache lines, of
+// which every line is read once and is not worth a place in the caches. 8 probes of 2048 frames of 256^2, c64, hop = L: L = 64
+// 1796 -> 1677 us, L = 512 2620 -> 2560; c128, 4 probes of 2000 frames of 128 x
+// 256, hop = L/2: L = 512 977 -> 901 us.
 #ifndef TACAW_WAVES_PER_EU
 #define TACAW_WAVES_PER_EU 1  // minimum waves per SIMD the register allocation must allow
 #endif
@@ -110,7 +114,8 @@ __global__ void __launch_bounds__(FftShape<L>::W*(L / FftShape<L>::N1))
   static_assert(!MIX || MODE == 1 || MODE == 3, "ring and push: the push-buffer variants");
   constexpr bool TILED = MODE == 4;
   constexpr bool RING = MODE == 2 || TILED;
-  constexpr bool NARROW = MODE == 3;
+  constexpr bool kNT = MODE == 5;
+  constexpr bool NARROW = MODE == 3 || kNT;
   constexpr int N1 = FftShape<L>::N1;
   constexpr int W = FftShape<L>::W;
   constexpr int N2 = L / N1;
@@ -204,7 +209,7 @@ __global__ void __launch_bounds__(FftShape<L>::W*(L / FftShape<L>::N1))
     if constexpr (NARROW) {
       const char* cb = (const char*)a.in + (int64_t)ii * a.pstride * ESZ +
                        ((int64_t)ss * H - a.push_begin) * row_bytes;
-      return buffer_load_so<InT>(cb, chunk_bytes, lane_off, (uint32_t)(N2 * n1 * row_bytes));
+      return buffer_load_so<InT, kNT>(cb, chunk_bytes, lane_off, (uint32_t)(N2 * n1 * row_bytes));
     } else if constexpr (RING) {
       // ring rows (ss H + N2 n1) mod D of probe probe0 + ii; D and H are multiples of
       // N2, so a row group never wraps (row_bytes is one frame of the ring here)
@@ -233,7 +238,7 @@ __global__ void __launch_bounds__(FftShape<L>::W*(L / FftShape<L>::N1))
       rb = (const char*)a.in + (int64_t)ii * a.pstride * ESZ +
            ((int64_t)ss * H - a.push_begin) * row_bytes + n1 * gstride;
     }
-    return buffer_load<InT>(rb, group_bytes, lane_off);
+    return buffer_load<InT, kNT>(rb, group_bytes, lane_off);
   };
   // sample n1 of the launch's first chunk of probe probe0 + ii; ring rows are
   // contiguous frames, and a row group (N2 frames, N2 dividing H and the depth)
