@@ -1475,10 +1475,14 @@ static int backward_impl(tacaw_plan_t P, const void* frames, int32_t probe0, int
                                        std::to_string(fixed_bytes) + " (16 n_probes n_k + 16 tiles)");
     work = (double*)fixed;
   } else if (need > P->scratch_bytes) {
+    // sized before the splits are evened out, which makes it grow with n_probes: a
+    // later call with fewer probes always fits
+    const int64_t room =
+        base + n_tiles * std::min<int64_t>(n_probes, (kFillTiles + n_tiles - 1) / n_tiles) * 16;
     P->release((void**)&P->scratch);
     P->scratch_bytes = 0;
-    TRY(P->alloc((void**)&P->scratch, need, "adjoint scratch"));
-    P->scratch_bytes = need;
+    TRY(P->alloc((void**)&P->scratch, room, "adjoint scratch"));
+    P->scratch_bytes = room;
     work = P->scratch;
   }
   BwdArgs b{};
