@@ -575,9 +575,25 @@ __global__ void __launch_bounds__(64 * kGemmWaves)
 // MFMAs; rows beyond 8 waves x 32 go to more row groups, each staging the same
 // frames (from L2 after the first)
 constexpr int kGemmNB = 4;
-static int gemm_groups(int n_om) {
+// Row groups of a launch: at least one per 8 blocks, and more where that leaves CUs
+// idle, in the only round of workgroups or in the last. Tiles are dealt to the 8 XCDs
+// of 32 CUs, a CU holds one workgroup, and a workgroup of b row blocks takes 3.6 + b
+// (512 tiles, 8 blocks in 1, 2, 3 or 4 groups: 3659, 4705, 6000, 7143 us: staging costs
+// a group as much as 3.6 blocks). 65 tiles of 32 blocks: 6904 us in 4 groups (36
+// workgroups on an XCD, two rounds), 4744 us in 7; 79 tiles of 8 blocks: 2154 us in 1
+// group, 1399 us in 3; 32 tiles of 32 blocks, whole call: 106 us in 4, 92 us in 8.
+static int gemm_groups(int n_om, int64_t n_tiles) {
   const int blocks = (2 * n_om + 31) / 32;
-  return (blocks + kGemmWaves - 1) / kGemmWaves;
+  const int64_t per_xcd = (n_tiles + 7) / 8;
+  int best = 0;
+  int64_t best_cost = 0;
+  for (int g = (blocks + kGemmWaves - 1) / kGemmWaves; g <= blocks; ++g) {
+    const int b = (blocks + g - 1) / g;
+    if ((blocks + b - 1) / b != g) continue;  // a group would be empty
+    const int64_t cost = (per_xcd * g + 31) / 32 * (18 + 5 * b);
+    if (!best || cost < best_cost) best = g, best_cost = cost;
+  }
+  return best;
 }
 
 template <int L, typename InT, int PREC, bool TRACK, int SRC>
@@ -602,7 +618,7 @@ template <int L, typename InT, int PREC>
 static hipError_t launch_g3(const SegArgs& a, const void* fmat, int m_rows, const float* gscale,
                             int n_tiles, hipStream_t st) {
   (void)n_tiles;  // the grid follows from n_k and the tile width
-  const int n_groups = gemm_groups(a.n_om);
+  const int n_groups = gemm_groups(a.n_om, (a.n_k + 32 * kGemmNB - 1) / (32 * kGemmNB));
   const int src = a.from_ring ? (a.ring_tiles > 0 ? 2 : 1)
                               : ((int64_t)a.s_lo * a.hop >= a.push_begin ? 0 : 1);
   if (a.track_mean) {

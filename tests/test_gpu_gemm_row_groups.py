@@ -44,3 +44,26 @@ def test_row_groups_match_oracle(form, dtype, ny, nx, M):
     plan.close()
     print(f"{form} {dtype} {ny}x{nx} M={M}: S {eS:.1e} D {eD:.1e} Dp {eDp:.1e}", flush=True)
     assert eS <= 1e-5 and eD <= 1e-5 and eDp <= 1e-5
+
+
+# a grid that fills the chip, so that a workgroup holds up to 8 row blocks (on smaller ones
+# the blocks are spread over more groups): 8, 9 and 17 blocks; against the FFT form
+@pytest.mark.parametrize("M", [63, 64, 128])
+@pytest.mark.parametrize("form", ["gemm_bf16x3", "gemm_f16x3"])
+def test_full_row_groups_match_fft_form(form, M):
+    from paper_2607_02236_amd import tacaw
+
+    L, H, P, ny, nx = 512, 256, 1, 128, 257
+    NT = 2 * L + 40
+    psi = T.generate(T.SeriesSpec(P, NT, ny, nx, dtype="c64", seed=M, model="lines", n_terms=8), device="cuda")
+    masks = torch.rand(1, ny, nx, dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(M))
+    out = []
+    for f in (form, "fft"):
+        plan = tacaw.Plan(P, ny, nx, NT, L, H, in_dtype="c64", transform=f, omega_half=M, masks=masks)
+        plan.push(psi)
+        S = plan.finalize().cpu().numpy()
+        D, Dp = plan.detector_spectra(per_probe=True)
+        out.append((S, D.cpu().numpy(), Dp.cpu().numpy()))
+        plan.close()
+    for x, y in zip(*out):
+        assert rel(x, y) <= 1e-5
