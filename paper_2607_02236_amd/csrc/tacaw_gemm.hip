@@ -66,8 +66,8 @@ __device__ __forceinline__ f32x16 mfma(h8 a, h8 b, f32x16 c) {
 //
 // Workgroup: 8 waves (two per SIMD), a tile of PX = 32 NB pixels and one row group
 // of the GEMM: wave w owns row block blk_lo + w (32 rows) of its group and holds
-// NB accumulator tiles of 32 x 32; as many groups as the rows need at 8 blocks
-// each. Frames are staged through LDS in stages of KC frames, converted to operand
+// NB accumulator tiles of 32 x 32; at most 8 blocks to a
+// group (gemm_groups). Frames are staged through LDS in stages of KC frames, converted to operand
 // order, in two alternating buffers (one barrier per stage).
 // Bound by the issue of one wave: in order, a wave alone issues a VALU instruction
 // every 5.5 to 8 cycles on this chip, two waves one every 3 to 5, and an MFMA (32
