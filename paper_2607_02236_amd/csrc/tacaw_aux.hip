@@ -166,10 +166,11 @@ __global__ void ring_store_kernel(const InT* in, int64_t pstride, int64_t fstrid
 // ((slot * n_tiles + k / W) * D + row) * W + k % W. A block moves R consecutive frames
 // (R = 16, or the largest power of two dividing D; the first frame aligned to R in
 // absolute frame index) of 1 KiB of pixels through LDS: a wave reads 1 KiB of one
-// frame and writes 1 KiB of consecutive rows of a tile (64 R bytes at W = 8), so
-// both sides are whole lines. Bound by memory. Copying straight from frames to rows
-// gave each wave four 256-byte reads and 16 separate 64-byte rows: 2 probes x 256
-// frames of 1024^2 pixels, 4.3 GB in and out, 2190 us, now 2000 us (4.3 TB/s; a plain copy reaches 4.76).
+// frame and writes 1 KiB of consecutive rows of a tile (64 R bytes at W = 8; half rows
+// where a row is 2 KiB), so both sides are whole lines. Bound by memory. Copying straight
+// from frames to rows gave each wave four 256-byte reads and 16 separate 64-byte rows: 2
+// probes x 256 frames of 1024^2 pixels, 4.3 GB in and out, 2190 us, now 2000 us (4.3 TB/s;
+// a plain copy reaches 4.76).
 // VEC: frames are contiguous and pixels come in pairs (complex64), so a thread moves
 // 16 bytes; otherwise element by element.
 constexpr int kStorePx = 1024;  // bytes of a frame per block
@@ -203,17 +204,19 @@ __global__ void __launch_bounds__(256) ring_store_tiled_kernel(
   }
   __syncthreads();
   const int slot = (probe0 + i) % n_slots;
-  const int wpr = tile_w / V;                 // 16-byte words per tile row
+  const int run = min(tile_w, PX);            // pixels of a tile row in this block
+  const int wpr = run / V;                    // 16-byte words of that run
   const int n_words = R * (kStorePx / 16);    // words of the block, [tile][row][word]
   const int64_t row0 = fb % depth;            // R divides D and fb: the rows do not wrap
   for (int e = threadIdx.x; e < n_words; e += 256) {
     const int part = e % wpr, r = (e / wpr) % R, t = e / (wpr * R);
-    const int64_t k0 = kb + (int64_t)t * tile_w + part * V;
+    const int64_t k0 = kb + (int64_t)t * run + part * V;
     const int64_t f = fb + r;
     if (k0 >= n_k || f < f_lo || f >= f_hi) continue;
     InT x[V];
     __builtin_memcpy(x, &buf[r * LROW + t * wpr + part], 16);
-    InT* dst = ring + (((int64_t)slot * n_tiles + k0 / tile_w) * depth + row0 + r) * tile_w + part * V;
+    const int64_t tile = k0 / tile_w;
+    InT* dst = ring + (((int64_t)slot * n_tiles + tile) * depth + row0 + r) * tile_w + (k0 - tile * tile_w);
     if (k0 + V <= n_k) {
       __builtin_memcpy(dst, x, 16);
     } else {
@@ -236,7 +239,9 @@ hipError_t launch_ring_store(const void* in, int in_dtype, int64_t pstride, int6
     while (depth % R != 0) R /= 2;
     const int esz = in_dtype == 1 ? 16 : 8;
     const int px = kStorePx / esz;
-    if (px % tile_w != 0 || tile_w % (16 / esz) != 0) return hipErrorInvalidValue;
+    // a block holds whole tile rows, or (128-pixel tiles of complex128) a part of one
+    if ((px % tile_w != 0 && tile_w % px != 0) || tile_w % (16 / esz) != 0)
+      return hipErrorInvalidValue;
     const int32_t n_tiles = (n_k + tile_w - 1) / tile_w;
     const int64_t fb = f_lo - f_lo % R;
     const dim3 g((unsigned)((n_k + px - 1) / px), (unsigned)((f_hi - fb + R - 1) / R), n_probes);
