@@ -176,6 +176,9 @@ typedef struct {
 /* Create a plan: validates desc on the host (no HIP call on failure), then
  * allocates the plan's FP64 accumulators on the current HIP device and records
  * hip_stream (a hipStream_t; NULL = default stream) for all later work.
+ * Waits for the work enqueued on the device before it, on any stream: d_masks, and
+ * frames made before the call, may come from other streams than hip_stream. Frames
+ * made later on another stream are the caller's to order.
  * Errors: INVALID_ARG, UNSUPPORTED, OOM, HIP. *out is NULL on error. */
 int tacaw_plan(const tacaw_plan_desc* desc, void* hip_stream, tacaw_plan_t* out);
 

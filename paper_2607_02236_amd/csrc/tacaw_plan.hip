@@ -748,9 +748,15 @@ int tacaw_plan(const tacaw_plan_desc* d, void* hip_stream, tacaw_plan_t* out) {
         make_dft_matrix(w, tr, d->transform == TACAW_GEMM_F16X3, P->n_om, P->roi, P->m_rows);
     put(P->fmat, fm.data(), (int64_t)fm.size() * 2);
   }
-  rc = hip_check(hipMemcpyAsync(P->arena, P->upload.data(), (size_t)table_bytes,
-                                hipMemcpyHostToDevice, P->st),
-                 "upload");
+  // Work enqueued on the device before the plan, on any stream, ends here: masks and
+  // frames made just before it on another stream than the plan's are whole when they
+  // are read, and what that stream still uses is not written over by the plan's.
+  // (Before the upload: behind it this wait cost a one-shot call 10 us.)
+  rc = hip_check(hipDeviceSynchronize(), "plan setup");
+  if (rc == TACAW_OK)
+    rc = hip_check(hipMemcpyAsync(P->arena, P->upload.data(), (size_t)table_bytes,
+                                  hipMemcpyHostToDevice, P->st),
+                   "upload");
   // what no launch writes reads as zero: the references and sums of plans that keep
   // none, and the correction bins that a rectangular window does not have
   if (rc == TACAW_OK)
