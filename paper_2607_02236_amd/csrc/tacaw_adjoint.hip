@@ -75,6 +75,10 @@ __device__ __forceinline__ float2 rot_g(float2 x, int e) {
   return e == 1 ? make_float2(x.y, -x.x) : make_float2(-x.y, x.x);
 }
 
+// Two waves share a SIMD up to 256 registers each. At L = 256 without DW the variants with
+// MT 2 are at that edge; one register over it (complex128) left one wave.
+constexpr int bwd_waves(int L, bool dw, int mt) { return L == 256 && !dw && mt == 2 ? 2 : 1; }
+
 // DW: the window-parameter derivative is wanted (dwin_t set). It needs the
 // centred samples again after both transforms: for complex64 input with
 // L <= 512 they stay in registers through the transforms (KEEP_Z); otherwise
@@ -94,7 +98,7 @@ __device__ __forceinline__ float2 rot_g(float2 x, int e) {
 // forward's sums of the next probe loaded a chunk ahead through LDS: no change.)
 template <int L, typename InT, bool DW, int MT, bool HALF_HOP>
 __global__ void __launch_bounds__(BwdShape<L>::W*(L / BwdShape<L>::N1))
-    bwd_kernel(const BwdArgs a) {
+    __attribute__((amdgpu_waves_per_eu(bwd_waves(L, DW, MT)))) bwd_kernel(const BwdArgs a) {
   constexpr int N1 = BwdShape<L>::N1;
   constexpr int W = BwdShape<L>::W;
   constexpr int N2 = L / N1;
@@ -110,9 +114,12 @@ __global__ void __launch_bounds__(BwdShape<L>::W*(L / BwdShape<L>::N1))
   __shared__ float2 s_tw[L];          // [n2][k1] exp(-2 pi i n2 k1 / L)
   __shared__ float s_win[L];          // [n2][n1]
   __shared__ float s_dwin[DW ? L : 1];
-  __shared__ double red[2 * NT];
+  __shared__ __attribute__((aligned(16))) double red[2 * NT];
   __shared__ float s_mk[kMaxDet * W];  // detector masks of the tile's pixels
-  __shared__ double2 s_mt[MT == 3 ? kMaxCorr * W : 1];  // MT 3: M_s terms per bin and pixel
+  // mean terms per correction bin and pixel, in the end's reduction array: L = 128 has no
+  // LDS to spare (four workgroups of 40960 bytes fill a CU)
+  static_assert(2 * NT >= 2 * kMaxCorr * W, "mean terms");
+  double2* const s_mt = reinterpret_cast<double2*>(red);
   float2* const xa = xbuf2;
   float2* const xi = xbuf2 + TILE;
 
@@ -192,48 +199,62 @@ __global__ void __launch_bounds__(BwdShape<L>::W*(L / BwdShape<L>::N1))
 #pragma unroll
   for (int n1 = 0; n1 < N1; ++n1) pre[n1] = buffer_load<InT>(group(a.in, i_lo, 0, n1), group_bytes, lane_off);
 
-  float gcorr[kMaxCorr];  // MT 2: the FP32 weights of the correction bins
+  float gcorr = 0.0f;  // MT 2: the FP32 weight of correction bin n2 (n2 < n_corr)
   for (int i = i_lo; i < i_hi; ++i) {
     const int p = a.probe0 + i;
     if (i == i_lo || a.gDp) {
 #pragma unroll
       for (int t = 0; t < N1; ++t) Gt[t] = (float)weight(bin(t), p);
-      if constexpr (MT == 2) {
-#pragma unroll
-        for (int b = 0; b < kMaxCorr; ++b)
-          gcorr[b] = b < a.n_corr ? (float)weight(b == 0 ? 0 : (b == 1 ? 1 : L - 1), p) : 0.0f;
+      if constexpr (MT == 2 && L < 1024) {
+        if (n2 < a.n_corr) gcorr = (float)weight(n2 == 0 ? 0 : (n2 == 1 ? 1 : L - 1), p);
       }
     }
     // mu = c + delta, delta = (sum over the used frames of psi - c) / N_used
     double2 mu = make_double2(0.0, 0.0), delta = make_double2(0.0, 0.0);
-    double2 xs[MT == 2 ? kMaxCorr : 1];
+    // The correction bins' weights and sums, once per probe, each by one thread of a
+    // pixel: held by every thread they took 15 registers, which left one wave per SIMD at
+    // L = 256, hop = L/2 (4 probes of 2048 frames of 128^2, c64, Hann: 829 us, now 561; with
+    // gDp 1450 -> 793) and spilled at L = 1024, where even this is too many: there each thread
+    // forms the weights and reads the sums in turn (1539 -> 1441 us, with DW 2070 -> 1928).
+    // Doing that at every L costs L = 512, hop = L 1059 -> 1185 us.
+    constexpr bool SHARE = L < 1024;
+    double2 xs = make_double2(0.0, 0.0);
     if constexpr (MT == 1 || MT == 2) {
       const double2 cr = a.cref[(int64_t)p * n_k + kc];
       const double2 ms = a.msum[(int64_t)p * n_k + kc];
-      if constexpr (MT == 2) {  // (all loads together)
-#pragma unroll
-        for (int b = 0; b < kMaxCorr; ++b)
-          if (b < a.n_corr) xs[b] = a.xs[((int64_t)p * kMaxCorr + b) * n_k + kc];
-      }
+      if (MT == 2 && SHARE && n2 < a.n_corr) xs = a.xs[((int64_t)p * kMaxCorr + n2) * n_k + kc];
       delta = make_double2(ms.x * a.inv_nused, ms.y * a.inv_nused);
       mu = make_double2(cr.x + delta.x, cr.y + delta.y);
     }
-    // MT 2: the mean term of this probe and pixel, divided by N_used
+    // MT 2: the mean term of this probe and pixel, divided by N_used: the sum over the
+    // correction bins b of g conj(W) (sx + i sy), sum_s X_s(m) = sum_s X'_s(m) - N_s delta W(m)
     float2 fix = make_float2(0.f, 0.f);
     double2 fixd = make_double2(0.0, 0.0);
     if constexpr (MT == 2) {
-      double2 gm = make_double2(0.0, 0.0);
-#pragma unroll
-      for (int b = 0; b < kMaxCorr; ++b) {
-        if (b >= a.n_corr) continue;
-        const double g = 2.0 * (double)gcorr[b];  // the FP32 weight the transform uses
-        const double2 wb = a.wbin[b];
-        const double2 x = xs[b];
-        // sum_s X_s(m) = sum_s X'_s(m) - N_s delta W(m)
+      auto term = [&](double gw, double2 wb, double2 x) {
+        const double g = 2.0 * gw;
         const double sx = x.x - a.n_seg * (delta.x * wb.x - delta.y * wb.y);
         const double sy = x.y - a.n_seg * (delta.x * wb.y + delta.y * wb.x);
-        gm.x += g * (wb.x * sx + wb.y * sy);  // g conj(W) (sx + i sy)
-        gm.y += g * (wb.x * sy - wb.y * sx);
+        return make_double2(g * (wb.x * sx + wb.y * sy), g * (wb.x * sy - wb.y * sx));
+      };
+      double2 gm = make_double2(0.0, 0.0);
+      if constexpr (SHARE) {
+        // the thread with role b < n_corr forms the share of bin b
+        if (n2 < a.n_corr)
+          s_mt[n2 * W + px] =
+              term((double)gcorr, n2 == 0 ? a.wbin[0] : (n2 == 1 ? a.wbin[1] : a.wbin[2]), xs);
+        __syncthreads();  // (the chunks' barriers keep the next probe's writes behind these reads)
+        for (int b = 0; b < a.n_corr; ++b) {
+          gm.x += s_mt[b * W + px].x;
+          gm.y += s_mt[b * W + px].y;
+        }
+      } else {
+        for (int b = 0; b < a.n_corr; ++b) {
+          const double2 t = term((double)(float)weight(b == 0 ? 0 : (b == 1 ? 1 : L - 1), p), a.wbin[b],
+                                 a.xs[((int64_t)p * kMaxCorr + b) * n_k + kc]);
+          gm.x += t.x;
+          gm.y += t.y;
+        }
       }
       fixd = make_double2(gm.x * a.inv_nused, gm.y * a.inv_nused);
       fix = make_float2((float)fixd.x, (float)fixd.y);
@@ -456,6 +477,7 @@ __global__ void __launch_bounds__(BwdShape<L>::W*(L / BwdShape<L>::N1))
     }
   }
   // workgroup partials of the r-derivative and the loss value
+  if constexpr (MT == 3) __syncthreads();  // the last chunk's reads of s_mt, in red, are done
   red[tid] = kvalid ? dA : 0.0;
   red[NT + tid] = kvalid ? dLval : 0.0;
   __syncthreads();
