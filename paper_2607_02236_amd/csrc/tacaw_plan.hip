@@ -193,8 +193,6 @@ struct tacaw_plan_s {
   std::vector<int> slot_owner;
   std::vector<std::pair<void**, int64_t>> owned;
   int64_t bytes = 0;
-  std::vector<char> upload;     // host side of the tables' copy
-  std::vector<int32_t> slots;   // host side of pair_slot
   // device buffers (arena: one allocation that holds those made with the plan)
   void* arena = nullptr;
   float* win_t = nullptr;   // [N2][N1]
@@ -713,9 +711,12 @@ int tacaw_plan(const tacaw_plan_desc* d, void* hip_stream, tacaw_plan_t* out) {
     return rc;
   }
   for (const Part& x : parts) *x.p = (char*)P->arena + x.off;
-  P->upload.assign((size_t)table_bytes, 0);  // kept by the plan: the copy is asynchronous
+  // host sides of the tables and of pair_slot: their copies are asynchronous, and the
+  // stream is waited for before the return, on every path (~tacaw_plan_s does so too)
+  std::vector<char> upload((size_t)table_bytes, 0);
+  std::vector<int32_t> slots;
   auto put = [&](const void* dst, const void* src, int64_t b) {
-    std::memcpy(P->upload.data() + ((const char*)dst - (const char*)P->arena), src, (size_t)b);
+    std::memcpy(upload.data() + ((const char*)dst - (const char*)P->arena), src, (size_t)b);
   };
   put(P->win_t, wt.data(), P->L * 4);
   put(P->dwin_t, dwt.data(), P->L * 4);
@@ -754,7 +755,7 @@ int tacaw_plan(const tacaw_plan_desc* d, void* hip_stream, tacaw_plan_t* out) {
   // (Before the upload: behind it this wait cost a one-shot call 10 us.)
   rc = hip_check(hipDeviceSynchronize(), "plan setup");
   if (rc == TACAW_OK)
-    rc = hip_check(hipMemcpyAsync(P->arena, P->upload.data(), (size_t)table_bytes,
+    rc = hip_check(hipMemcpyAsync(P->arena, upload.data(), (size_t)table_bytes,
                                   hipMemcpyHostToDevice, P->st),
                    "upload");
   // what no launch writes reads as zero: the references and sums of plans that keep
@@ -769,7 +770,7 @@ int tacaw_plan(const tacaw_plan_desc* d, void* hip_stream, tacaw_plan_t* out) {
       rc = hip_check(hipMemcpy(hm.data(), P->masks, hm.size() * 8, hipMemcpyDeviceToHost), "mask read");
     // one partial slot per (tile, detector) whose mask is non-zero on the tile,
     // numbered detector by detector so each detector's slots are contiguous
-    P->slots.assign((size_t)P->n_tiles * d->n_det, -1);
+    slots.assign((size_t)P->n_tiles * d->n_det, -1);
     int act = 0;
     for (int dd = 0; dd < d->n_det; ++dd) {
       P->det_slots.off[dd] = act;
@@ -777,7 +778,7 @@ int tacaw_plan(const tacaw_plan_desc* d, void* hip_stream, tacaw_plan_t* out) {
         const int64_t k1 = std::min<int64_t>(nk, (int64_t)(t + 1) * P->W);
         for (int64_t k = (int64_t)t * P->W; k < k1; ++k)
           if (hm[(size_t)dd * nk + k] != 0.0) {
-            P->slots[(size_t)t * d->n_det + dd] = act++;
+            slots[(size_t)t * d->n_det + dd] = act++;
             break;
           }
       }
@@ -785,7 +786,7 @@ int tacaw_plan(const tacaw_plan_desc* d, void* hip_stream, tacaw_plan_t* out) {
     P->det_slots.off[d->n_det] = act;
     P->n_pairs = act;
     if (rc == TACAW_OK)
-      rc = hip_check(hipMemcpyAsync(P->pair_slot, P->slots.data(), P->slots.size() * 4,
+      rc = hip_check(hipMemcpyAsync(P->pair_slot, slots.data(), slots.size() * 4,
                                     hipMemcpyHostToDevice, P->st),
                      "upload");
   }
