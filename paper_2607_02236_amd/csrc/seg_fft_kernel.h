@@ -304,6 +304,11 @@ __global__ void __launch_bounds__(FftShape<L>::W*(L / FftShape<L>::N1))
     float2 kept[HALF];
     bool have_kept = false;
 
+    // MODE 0: ring row of the chunk's first frame (H <= D). A 64-bit remainder per sample
+    // here made the kernel 78 KB long, more than the instruction cache: the same code took
+    // 4516 or 4954 us by where it was placed (4 probes of 2048 frames of 256^2, L = 128, hop 32).
+    const int ring_d = (int)a.ring_depth;
+    int ring_row = a.ring_row_lo;
     for (int s = a.s_lo; s < a.s_hi; ++s) {
       const int64_t seg0 = (int64_t)s * H;
       const bool fast = LEAN || seg0 >= a.push_begin;
@@ -396,7 +401,10 @@ __global__ void __launch_bounds__(FftShape<L>::W*(L / FftShape<L>::N1))
         const int64_t f = seg0 + N2 * n1 + n2;
         if (f >= a.push_begin)
           return *(const InT*)(in_probe + (f - a.push_begin) * row_bytes + kin * ESZ);
-        return ringb[(f % a.ring_depth) * (int64_t)n_k];
+        // ring row of frame f: L <= D, so it wraps at most once from the chunk's first row
+        int row = ring_row + N2 * n1 + n2;
+        if (row >= ring_d) row -= ring_d;
+        return ringb[(int64_t)row * n_k];
       };
       auto load_range = [&](int lo, auto fetch, auto cmode) {
 #pragma unroll
@@ -631,6 +639,10 @@ __global__ void __launch_bounds__(FftShape<L>::W*(L / FftShape<L>::N1))
             if (!a.corr_skip) acc[N1 - 1] += sq64(X[N1 - 1]);
           }
         }
+      }
+      if constexpr (!LEAN) {
+        ring_row += H;
+        if (ring_row >= ring_d) ring_row -= ring_d;
       }
     }
 
