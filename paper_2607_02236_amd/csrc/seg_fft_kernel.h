@@ -287,14 +287,22 @@ __global__ void __launch_bounds__(FftShape<L>::W*(L / FftShape<L>::N1))
   };
   int cc = 0;  // chunks processed by this thread block (selects the exchange tile)
   // reference c: fixed by the probe's first chunk (make_ref below) or read back, one
-  // probe ahead
+  // probe ahead; by the general variant for complex64 at the probe's start, as the 4
+  // registers would leave it one wave per SIMD at L = 128 and 256 (4 probes of 2048 frames
+  // of 256^2, hop L/4: 4546 and 4944 us, read at the start 2817 and 2706). The others gain by
+  // reading ahead: 256 probes of 64^2, one chunk each, L = 64, exact mean, 916 -> 655 us.
+  constexpr bool AHEAD = LEAN || ESZ == 16;
   const bool read_ref = !(track && a.s_lo == 0);
   double2 cr_next = make_double2(0.0, 0.0);
-  if (read_ref) cr_next = a.cref[(int64_t)a.probe0 * n_k + kc];
+  if (AHEAD && read_ref) cr_next = a.cref[(int64_t)a.probe0 * n_k + kc];
   for (int i = 0; i < a.n_probes; ++i) {
     const int p = a.probe0 + i;
     double2 cr = cr_next;
-    if (read_ref && i + 1 < a.n_probes) cr_next = a.cref[(int64_t)(p + 1) * n_k + kc];
+    if constexpr (AHEAD) {
+      if (read_ref && i + 1 < a.n_probes) cr_next = a.cref[(int64_t)(p + 1) * n_k + kc];
+    } else if (read_ref) {
+      cr = a.cref[(int64_t)p * n_k + kc];
+    }
     float2 cf = make_float2((float)cr.x, (float)cr.y);
     const char* in_probe = (const char*)a.in + (int64_t)i * a.pstride * ESZ;
     const InT* ringb =
