@@ -592,9 +592,12 @@ __global__ void __launch_bounds__(FftShape<L>::W*(L / FftShape<L>::N1))
           auto cl = [&](int n) { return col[n * W]; };
           if (gg == 0) dif_combine<N1, 2, 0>(cl, X);
           else dif_combine<N1, 2, 1>(cl, X);
-        } else if constexpr (!LEAN || MIX) {
-          // (a pushed series: one code path for every chunk of it, as the roundings of
-          // the two G = 4 paths differ in the twiddle row)
+        } else if constexpr (!LEAN) {
+          // (The roundings of the two G = 4 paths differ in the twiddle row. All chunks of a
+          // series take the same one however it is pushed: its plan's hop, and whether its
+          // ring is deferred, decide if this variant serves it. The pushed variants had this path
+          // too, with a few registers less: 2 probes of 4096 frames of 256^2 in pushes of 512, c64
+          // 7700 us, now 7767; c128, 2048 frames of 128 x 256, 2053, now 2109.)
           auto cl = [&](int n) { return col[n * W]; };
           if (gg == 0) dif_combine<N1, 4, 0>(cl, X);
           else if (gg == 1) dif_combine<N1, 4, 1>(cl, X);
