@@ -911,9 +911,10 @@ __global__ void detector_kernel(const double* S, const double* masks, int32_t L,
 template <int ND>
 static void launch_det_nd(const double* S, const double* masks, int32_t L, int32_t n_k,
                           double kappa, const double* q, double* D, hipStream_t st) {
-  // 16384 pixels per block, fewer while the grid is below 8 blocks per CU, but at most
-  // 32 blocks add to one value (256^2 pixels, 123 bins, 4 masks: 47 us with 16384 pixels per
-  // block, 29 us with 2048, 181 us with 512 and one atomic per wave, which queue up)
+  // 16384 pixels per block, fewer while the grid is below 8 blocks per CU and no more than
+  // 32 blocks then add to one value (256^2 pixels, 123 bins, 4 masks: 47 us with 16384 pixels per
+  // block, 29 us with 2048, 181 us with 512 and one atomic per wave, which queue up). Grids
+  // above 2^19 pixels keep 16384 and add more: 64 blocks at 1024^2
   const int64_t rows = (L + kDetBins - 1) / kDetBins;
   int chunk = 16384;
   while (chunk > 512 && (n_k + chunk - 1) / chunk * rows < 2048 && n_k <= 32 * (chunk / 2)) chunk /= 2;

@@ -1,7 +1,7 @@
-"""DFT-GEMM form at the edges of its row groups (8 blocks of 32 GEMM rows per
-workgroup, 16 output rows per block) and pixel tiles (128): one block, one row into the
-next block, a full group, one row into a second group, uneven groups; with waves
-that only stage, detector partials and several probes."""
+"""DFT-GEMM form at the edges of its row blocks (32 GEMM rows, 16 output rows, at most 8
+blocks per workgroup) and pixel tiles (128): one block, one row into the next block, 8, 9
+and 17 blocks, which such small grids spread one to a group; with waves that only
+stage, detector partials and several probes. (Groups of 8: test_gpu_gemm_full_groups.py.)"""
 
 import numpy as np
 import pytest
@@ -17,7 +17,7 @@ def rel(a, b):
     return float(np.linalg.norm((np.asarray(a) - np.asarray(b)).ravel()) / np.linalg.norm(np.asarray(b).ravel()))
 
 
-# output rows 2 M + 1: 15, 17 (blocks 1, 2), 127, 129 (8, 9: one and two groups), 257 (17: three)
+# output rows 2 M + 1: 15, 17 (1 and 2 blocks), 127, 129 (8 and 9), 257 (17)
 @pytest.mark.parametrize("M", [7, 8, 63, 64, 128])
 @pytest.mark.parametrize("form,dtype,ny,nx", [("gemm_bf16x3", "c64", 11, 12), ("gemm_bf16x3", "c128", 8, 16),
                                               ("gemm_f16x3", "c64", 3, 43)])
@@ -46,8 +46,8 @@ def test_row_groups_match_oracle(form, dtype, ny, nx, M):
     assert eS <= 1e-5 and eD <= 1e-5 and eDp <= 1e-5
 
 
-# a grid that fills the chip, so that a workgroup holds up to 8 row blocks (on smaller ones
-# the blocks are spread over more groups): 8, 9 and 17 blocks; against the FFT form
+# 257 tiles, one more than a round of workgroups: 8, 9 and 17 blocks in groups of 4, 5 and 6;
+# against the FFT form
 @pytest.mark.parametrize("M", [63, 64, 128])
 @pytest.mark.parametrize("form", ["gemm_bf16x3", "gemm_f16x3"])
 def test_full_row_groups_match_fft_form(form, M):
